@@ -13,14 +13,6 @@ namespace rose {
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float f32x16_t __attribute__((ext_vector_type(16)));
 
-// float -> bfloat16, round to nearest even (NaN kept quiet)
-__device__ inline unsigned short to_bf16(float f) {
-    uint32_t u = __float_as_uint(f);
-    if ((u & 0x7f800000u) == 0x7f800000u) return (unsigned short)((u >> 16) | ((u & 0xffffu) ? 0x40u : 0u));
-    u += 0x7fffu + ((u >> 16) & 1u);
-    return (unsigned short)(u >> 16);
-}
-
 __device__ inline float gelu_f(float z) { return 0.5f * z * (1.0f + erff(z * 0.70710678118654752f)); }
 
 __device__ inline float gelu_grad_f(float z) {
@@ -43,53 +35,106 @@ struct GemmArgs {
     int32_t mode;
 };
 
-constexpr int kGT = 64;  // block tile (M and N)
-constexpr int kKT = 32;  // K tile
-constexpr int kKP = kKT + 8;  // LDS row pitch (elements): 80-byte rows keep 16-byte reads aligned
-
-// 256 threads = 2x2 wavefronts, each owning a 32x32 sub-tile computed with
-// gfx950's double-K v_mfma_f32_32x32x16_bf16 (K = 16 per instruction).
+// Products: C = A B with binary32 operands rounded to bfloat16 on their way
+// into LDS and gfx950's double-K v_mfma_f32_32x32x16_bf16.  Every output
+// element is one chain of these instructions over ascending k whatever the
+// kernel and tile, so a product's bits do not depend on which one runs it.
 // Operand layout: lane l holds A[l % 32][8 (l / 32) .. +7] and
 // B[8 (l / 32) .. +7][l % 32]; the 16 accumulators of lane l are
 // D[8 (i / 4) + 4 (l / 32) + i % 4][l % 32].
-__global__ __launch_bounds__(256) void k_gemm_bf16(GemmArgs g) {
-    __shared__ __attribute__((aligned(16))) unsigned short As[kGT][kKP];
-    __shared__ __attribute__((aligned(16))) unsigned short Bs[kGT][kKP];  // transposed: [n][k]
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int wm = wave >> 1, wn = wave & 1;
-    const int m0 = blockIdx.y * kGT, n0 = blockIdx.x * kGT;
-    f32x16_t acc;
+//
+// An LDS tile holds rows of kc bfloat16 (kc a multiple of 32) in 16-byte
+// chunks of 8 consecutive k, the unit that is written (one chunk per lane
+// from 8 binary32 values) and read back as an MFMA operand.  Chunk c of row
+// r lies at position c ^ ((r / 2) mod 4) within its row: 8 lanes that read
+// the same chunk of 8 consecutive rows then touch 8 different bank groups.
+__device__ inline int chunk_at(int row, int c, int kc) { return row * (kc / 8) + (c ^ ((row >> 1) & 3)); }
+
+// How an operand lies in memory, as rows (m or n) by k.
+enum { LD_K = 0,     // k contiguous: two 16-byte loads per chunk, lanes along k
+       LD_ROW = 1 }; // any other strides: 8 loads per chunk, lanes along the rows
+
+struct OpView {
+    const float* p;
+    int64_t srow, sk;
+    int32_t rows, K;
+};
+
+typedef float f32x4_t __attribute__((ext_vector_type(4)));
+typedef f32x4_t f32x4u_t __attribute__((aligned(4)));  // 16-byte loads need 4-byte alignment only
+
+// the 8 values of row r at k .. k + 7 (0 past the matrix)
+template <int LD>
+__device__ inline void load_chunk(const OpView& o, int r, int k, float (&v)[8]) {
+    if (r < o.rows && k + 8 <= o.K) {
+        const float* q = o.p + r * o.srow + k * o.sk;
+        if constexpr (LD == LD_K) {
+            const f32x4_t a = *(const f32x4u_t*)q, b = *(const f32x4u_t*)(q + 4);
 #pragma unroll
-    for (int i = 0; i < 16; ++i) acc[i] = 0.0f;
-    for (int k0 = 0; k0 < g.K; k0 += kKT) {
-        for (int e = threadIdx.x; e < kGT * kKT; e += 256) {
-            const int r = e / kKT, c = e % kKT;
-            const int m = m0 + r, k = k0 + c;
-            As[r][c] = to_bf16((m < g.M && k < g.K) ? g.A[m * g.sam + k * g.sak] : 0.0f);
-        }
-        for (int e = threadIdx.x; e < kGT * kKT; e += 256) {
-            const int c = e / kGT, r = e % kGT;  // consecutive threads walk n
-            const int n = n0 + r, k = k0 + c;
-            Bs[r][c] = to_bf16((n < g.N && k < g.K) ? g.B[k * g.sbk + n * g.sbn] : 0.0f);
-        }
-        __syncthreads();
-#pragma unroll
-        for (int kk = 0; kk < kKT; kk += 16) {
-            const int ml = wm * 32 + (lane & 31), nl = wn * 32 + (lane & 31), kb = kk + 8 * (lane >> 5);
-            bf16x8_t a, b;
-#pragma unroll
-            for (int q = 0; q < 8; ++q) {
-                a[q] = __builtin_bit_cast(__bf16, As[ml][kb + q]);
-                b[q] = __builtin_bit_cast(__bf16, Bs[nl][kb + q]);
+            for (int e = 0; e < 4; ++e) {
+                v[e] = a[e];
+                v[4 + e] = b[e];
             }
-            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, acc, 0, 0, 0);
+        } else {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) v[e] = q[e * o.sk];
         }
-        __syncthreads();
+    } else {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] = (r < o.rows && k + e < o.K) ? o.p[r * o.srow + (k + e) * o.sk] : 0.0f;
     }
+}
+
+// The same through a raw buffer that starts at the tile's first row: a
+// 32-bit offset per chunk, held for the whole product, plus a wave-uniform
+// offset of the k-step.  kNoRow marks a chunk past the last row: at or past
+// the buffer's size with every k-step added, it reads 0.  The launch keeps
+// every offset of a tile (rows and k together) below kNoRow.
+constexpr uint32_t kNoRow = 0x80000000u;
+
+__device__ inline __amdgpu_buffer_rsrc_t tile_buffer(const OpView& o, int row0) {
+    return __builtin_amdgcn_make_buffer_rsrc((void*)(o.p + row0 * o.srow), (short)0, (int)kNoRow, 0x00020000);
+}
+
+template <int LD>
+__device__ inline void load_chunk(__amdgpu_buffer_rsrc_t b, uint32_t off, uint32_t k_bytes, uint32_t sk_bytes,
+                                  float (&v)[8]) {
+    if constexpr (LD == LD_K) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const auto a = __builtin_amdgcn_raw_buffer_load_b128(b, (int)(off + 16 * h), (int)k_bytes, 0);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[4 * h + e] = __uint_as_float(a[e]);
+        }
+    } else {
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+            v[e] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(b, (int)off, (int)(k_bytes + e * sk_bytes), 0));
+    }
+}
+
+// a chunk of which only the first `left` values are inside the matrix
+__device__ inline void load_chunk_tail(__amdgpu_buffer_rsrc_t b, uint32_t off, uint32_t k_bytes, uint32_t sk_bytes,
+                                       int left, float (&v)[8]) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e)
+        v[e] = __uint_as_float(
+            __builtin_amdgcn_raw_buffer_load_b32(b, (int)(e < left ? off : kNoRow), (int)(k_bytes + e * sk_bytes), 0));
+}
+
+// 8 binary32 values as a chunk of 8 bfloat16 (round to nearest even)
+__device__ inline bf16x8_t to_chunk(const float (&v)[8]) {
+    bf16x8_t c;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) c[e] = (__bf16)v[e];
+    return c;
+}
+
+__device__ inline void epilogue(const GemmArgs& g, const f32x16_t& acc, int mt, int nt, int lane) {
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
-        const int m = m0 + wm * 32 + 8 * (i / 4) + 4 * (lane >> 5) + (i % 4);
-        const int n = n0 + wn * 32 + (lane & 31);
+        const int m = mt + 8 * (i / 4) + 4 * (lane >> 5) + (i % 4);
+        const int n = nt + (lane & 31);
         if (m >= g.M || n >= g.N) continue;
         const int64_t o = m * g.ldc + n;
         const float v = acc[i];
@@ -105,6 +150,191 @@ __global__ __launch_bounds__(256) void k_gemm_bf16(GemmArgs g) {
             g.C[o] = v * gelu_grad_f(g.Z[o]);
         }
     }
+}
+
+// Large products: a BM x BN tile per workgroup, WM x WN of it per wavefront.
+// Bound by the binary32 operands on their way from L2 into the CU: a k-step
+// of 32 moves (BM + BN) 128 bytes for BM BN 64 flops, which at 64 B per
+// clock is as long as its matrix instructions take with 256 x 256.  The next
+// step's values are loaded into registers before this step's matrix
+// instructions and written to the other LDS buffer after them (one barrier
+// per step).  4096^3 with 256 x 256: 0.219 ms, 627 TFLOP/s (1.74 ms, 79
+// TFLOP/s, with one 64 x 64 tile, 4-byte loads and no load ahead).
+template <int BM, int BN, int WM, int WN, int LA, int LB>
+__global__ __launch_bounds__((BM / WM) * (BN / WN) * 64) void k_gemm_tile(GemmArgs g) {
+    constexpr int kThreads = (BM / WM) * (BN / WN) * 64, KC = 32, TM = WM / 32, TN = WN / 32;
+    constexpr int CA = BM * (KC / 8) / kThreads, CB = BN * (KC / 8) / kThreads;  // chunks per thread
+    __shared__ bf16x8_t As[2][BM * (KC / 8)];
+    __shared__ bf16x8_t Bs[2][BN * (KC / 8)];
+    // XCD x (workgroup index mod 8) takes a contiguous run of the tile list,
+    // which goes down 4 tile rows before it moves to the next column: the
+    // tiles in flight on an XCD share their operands in its L2
+    const int nt = (g.N + BN - 1) / BN, mt = (g.M + BM - 1) / BM, total = nt * mt;
+    int t;
+    {
+        const int b = blockIdx.x, x = b & 7, per = total >> 3, rem = total & 7;
+        t = x * per + min(x, rem) + (b >> 3);
+    }
+    const int band = t / (4 * nt), rows_in = min(4, mt - 4 * band), in = t - band * 4 * nt;
+    const int m0 = (4 * band + in % rows_in) * BM, n0 = (in / rows_in) * BN;
+    const OpView A{g.A, g.sam, g.sak, g.M, g.K}, B{g.B, g.sbn, g.sbk, g.N, g.K};
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int wm = (wave / (BN / WN)) * WM, wn = (wave % (BN / WN)) * WN;
+    f32x16_t acc[TM][TN];
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.0f;
+    float va[CA][8], vb[CB][8];
+    const __amdgpu_buffer_rsrc_t ra = tile_buffer(A, m0), rb = tile_buffer(B, n0);
+    const uint32_t ska = 4u * (uint32_t)g.sak, skb = 4u * (uint32_t)g.sbk;
+    uint32_t oa[CA], ob[CB];
+#pragma unroll
+    for (int q = 0; q < CA; ++q) {
+        const int e = tid + q * kThreads, r = LA == LD_ROW ? e % BM : e / 4, c = LA == LD_ROW ? e / BM : e % 4;
+        oa[q] = m0 + r < g.M ? 4u * (uint32_t)g.sam * r + 8u * ska * c : kNoRow;
+    }
+#pragma unroll
+    for (int q = 0; q < CB; ++q) {
+        const int e = tid + q * kThreads, r = LB == LD_ROW ? e % BN : e / 4, c = LB == LD_ROW ? e / BN : e % 4;
+        ob[q] = n0 + r < g.N ? 4u * (uint32_t)g.sbn * r + 8u * skb * c : kNoRow;
+    }
+    auto fetch = [&](int k0) {
+        if (k0 + KC <= g.K) {
+#pragma unroll
+            for (int q = 0; q < CA; ++q) load_chunk<LA>(ra, oa[q], k0 * ska, ska, va[q]);
+#pragma unroll
+            for (int q = 0; q < CB; ++q) load_chunk<LB>(rb, ob[q], k0 * skb, skb, vb[q]);
+        } else {  // the last, partial step
+#pragma unroll
+            for (int q = 0; q < CA; ++q) {
+                const int e = tid + q * kThreads, c = LA == LD_ROW ? e / BM : e % 4;
+                load_chunk_tail(ra, oa[q], k0 * ska, ska, g.K - k0 - 8 * c, va[q]);
+            }
+#pragma unroll
+            for (int q = 0; q < CB; ++q) {
+                const int e = tid + q * kThreads, c = LB == LD_ROW ? e / BN : e % 4;
+                load_chunk_tail(rb, ob[q], k0 * skb, skb, g.K - k0 - 8 * c, vb[q]);
+            }
+        }
+    };
+    auto stage = [&](int buf) {
+#pragma unroll
+        for (int q = 0; q < CA; ++q) {
+            const int e = tid + q * kThreads, r = LA == LD_ROW ? e % BM : e / 4, c = LA == LD_ROW ? e / BM : e % 4;
+            As[buf][chunk_at(r, c, KC)] = to_chunk(va[q]);
+        }
+#pragma unroll
+        for (int q = 0; q < CB; ++q) {
+            const int e = tid + q * kThreads, r = LB == LD_ROW ? e % BN : e / 4, c = LB == LD_ROW ? e / BN : e % 4;
+            Bs[buf][chunk_at(r, c, KC)] = to_chunk(vb[q]);
+        }
+    };
+    fetch(0);
+    stage(0);
+    __syncthreads();
+    int buf = 0;
+    for (int k0 = 0; k0 < g.K; k0 += KC, buf ^= 1) {
+        const bool more = k0 + KC < g.K;
+        if (more) fetch(k0 + KC);
+#pragma unroll
+        for (int kk = 0; kk < KC / 16; ++kk) {
+            bf16x8_t a[TM], b[TN];
+#pragma unroll
+            for (int i = 0; i < TM; ++i) a[i] = As[buf][chunk_at(wm + 32 * i + (lane & 31), 2 * kk + (lane >> 5), KC)];
+#pragma unroll
+            for (int j = 0; j < TN; ++j) b[j] = Bs[buf][chunk_at(wn + 32 * j + (lane & 31), 2 * kk + (lane >> 5), KC)];
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int j = 0; j < TN; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
+        }
+        if (more) stage(buf ^ 1);
+        __syncthreads();
+    }
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) epilogue(g, acc[i][j], m0 + wm + 32 * i, n0 + wn + 32 * j, lane);
+}
+
+// Small products (the network's): one 32 x 32 tile per workgroup, so that
+// also a few rows or columns spread over the chip.  Bound by the latency of
+// the loads: the 8 wavefronts together fetch kSmallK columns of both
+// operands at once (all loads of a stage in flight, the next stage's before
+// this stage's matrix instructions), and wavefront 0 runs the chain of
+// matrix instructions over them.  One row through the network: 17 us for its
+// three products (127 us with 64 x 64 tiles and 38 dependent loads per
+// product); a 1024-sample training step 153 us (809 us).
+constexpr int kSmallK = 256;
+template <int LA, int LB>
+__global__ __launch_bounds__(512) void k_gemm_small(GemmArgs g) {
+    constexpr int KC = kSmallK, CH = 32 * (KC / 8) / 512;  // chunks per thread and operand
+    __shared__ bf16x8_t As[2][32 * (KC / 8)];
+    __shared__ bf16x8_t Bs[2][32 * (KC / 8)];
+    const int m0 = blockIdx.y * 32, n0 = blockIdx.x * 32;
+    const OpView A{g.A, g.sam, g.sak, g.M, g.K}, B{g.B, g.sbn, g.sbk, g.N, g.K};
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    f32x16_t acc;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) acc[i] = 0.0f;
+    float va[CH][8], vb[CH][8];
+    auto at = [&](int ld, int q, int* r, int* c) {
+        const int e = tid + q * 512;
+        *r = ld == LD_ROW ? e % 32 : e / (KC / 8);
+        *c = ld == LD_ROW ? e / 32 : e % (KC / 8);
+    };
+    auto fetch = [&](int k0) {
+        int r, c;
+#pragma unroll
+        for (int q = 0; q < CH; ++q) {
+            at(LA, q, &r, &c);
+            load_chunk<LA>(A, m0 + r, k0 + 8 * c, va[q]);
+        }
+#pragma unroll
+        for (int q = 0; q < CH; ++q) {
+            at(LB, q, &r, &c);
+            load_chunk<LB>(B, n0 + r, k0 + 8 * c, vb[q]);
+        }
+    };
+    fetch(0);
+    int buf = 0;
+    for (int k0 = 0; k0 < g.K; k0 += KC, buf ^= 1) {
+        int r, c;
+#pragma unroll
+        for (int q = 0; q < CH; ++q) {
+            at(LA, q, &r, &c);
+            As[buf][chunk_at(r, c, KC)] = to_chunk(va[q]);
+        }
+#pragma unroll
+        for (int q = 0; q < CH; ++q) {
+            at(LB, q, &r, &c);
+            Bs[buf][chunk_at(r, c, KC)] = to_chunk(vb[q]);
+        }
+        // the other buffer's readers (wavefront 0, one stage back) passed
+        // this barrier after their reads, so two buffers need one barrier
+        __syncthreads();
+        if (k0 + KC < g.K) fetch(k0 + KC);
+        if (wave == 0) {
+            // 8 instructions' operands at a time, so that the chain does not
+            // wait for LDS between them (past K the chunks hold zeros)
+            const int steps = min(KC / 16, (g.K - k0 + 15) / 16);
+            for (int kb = 0; kb < steps; kb += 8) {
+                bf16x8_t a[8], b[8];
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    a[e] = As[buf][chunk_at(lane & 31, 2 * (kb + e) + (lane >> 5), KC)];
+                    b[e] = Bs[buf][chunk_at(lane & 31, 2 * (kb + e) + (lane >> 5), KC)];
+                }
+#pragma unroll
+                for (int e = 0; e < 8; ++e) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[e], b[e], acc, 0, 0, 0);
+            }
+        }
+    }
+    if (wave == 0) epilogue(g, acc, m0, n0, lane);
 }
 
 // Gaussian NLL per sample and its gradient w.r.t. the 12 outputs (scaled by
@@ -167,12 +397,43 @@ __global__ __launch_bounds__(256) void k_adam(int64_t n, float* p, const float* 
     p[i] = p[i] - lr * (mi / c1) / (sqrtf(vi / c2) + eps);
 }
 
+// whether every offset of a 256-row tile of an operand, over all k, fits the
+// tile kernels' 32-bit buffer offsets
+static bool tile_fits(int64_t srow, int64_t sk, int32_t K) {
+    if (srow < 0 || sk < 0 || srow >= (1 << 21) || sk >= (1 << 29)) return false;
+    return 4 * (256 * srow + (int64_t)(K + 32) * sk) < (int64_t)kNoRow;
+}
+
+// Kernel by output size and K (rows and columns contiguous in memory, us):
+//   4096^2 x 4096  256: 210, 128: 264, 64: 420, small: 1052   (256 tiles of 256)
+//   4096 x 2048 x 4096  256: 183, 128: 112, 64: 206
+//   2048 x 1024 x 2048  128: 58, 64: 38, small: 78             (128 tiles of 128)
+//   1024^2 x 1024  128: 29, 64: 17, small: 23                  (256 tiles of 64)
+//   512^2 x 2048  64: 27, small: 20; 1024 x 256 x 1216  64: 18, small: 15
+//   4096^2 x 128  256: 41, 128: 33, 64: 23 (few k-steps: the stores count,
+//   and more workgroups overlap them with other tiles' products)
+// so a wider tile is taken once it leaves (almost) every CU a workgroup --
+// two of them with 128 x 128, whose waves alone do not hide their loads.
+template <int LA, int LB>
+static void launch_gemm(const GemmArgs& g, hipStream_t s) {
+    auto tiles = [&](int t) { return (int64_t)((g.M + t - 1) / t) * ((g.N + t - 1) / t); };
+    const bool fits = tile_fits(g.sam, g.sak, g.K) && tile_fits(g.sbn, g.sbk, g.K);
+    if (fits && g.K >= 512 && tiles(256) >= 192)
+        hipLaunchKernelGGL((k_gemm_tile<256, 256, 128, 64, LA, LB>), dim3((unsigned)tiles(256)), dim3(512), 0, s, g);
+    else if (fits && g.K >= 512 && tiles(128) >= 256)
+        hipLaunchKernelGGL((k_gemm_tile<128, 128, 64, 64, LA, LB>), dim3((unsigned)tiles(128)), dim3(256), 0, s, g);
+    else if (fits && tiles(64) >= 192)
+        hipLaunchKernelGGL((k_gemm_tile<64, 64, 32, 32, LA, LB>), dim3((unsigned)tiles(64)), dim3(256), 0, s, g);
+    else
+        hipLaunchKernelGGL((k_gemm_small<LA, LB>), dim3((g.N + 31) / 32, (g.M + 31) / 32), dim3(512), 0, s, g);
+}
+
 static rose_status gemm(int M, int N, int K, const float* A, int64_t sam, int64_t sak, const float* B, int64_t sbk,
                         int64_t sbn, float* C, int64_t ldc, int mode, const float* bias, float* H, const float* Z,
                         hipStream_t s) {
     GemmArgs g{M, N, K, A, sam, sak, B, sbk, sbn, C, ldc, bias, H, Z, mode};
-    dim3 grid((N + kGT - 1) / kGT, (M + kGT - 1) / kGT);
-    hipLaunchKernelGGL(k_gemm_bf16, grid, dim3(256), 0, s, g);
+    if (sak == 1) sbk == 1 ? launch_gemm<LD_K, LD_K>(g, s) : launch_gemm<LD_K, LD_ROW>(g, s);
+    else sbk == 1 ? launch_gemm<LD_ROW, LD_K>(g, s) : launch_gemm<LD_ROW, LD_ROW>(g, s);
     ROSE_CHECK_HIP(hipGetLastError());
     return ROSE_OK;
 }
