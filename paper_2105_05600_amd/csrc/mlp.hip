@@ -45,10 +45,14 @@ struct GemmArgs {
 //
 // An LDS tile holds rows of kc bfloat16 (kc a multiple of 32) in 16-byte
 // chunks of 8 consecutive k, the unit that is written (one chunk per lane
-// from 8 binary32 values) and read back as an MFMA operand.  Chunk c of row
-// r lies at position c ^ ((r / 2) mod 4) within its row: 8 lanes that read
-// the same chunk of 8 consecutive rows then touch 8 different bank groups.
-__device__ inline int chunk_at(int row, int c, int kc) { return row * (kc / 8) + (c ^ ((row >> 1) & 3)); }
+// from 8 binary32 values) and read back as an MFMA operand.  Within its row
+// chunk c of row r lies at c ^ (r mod 8), or with 4 chunks per row at
+// c ^ ((r / 2) mod 4): 8 lanes that touch the same chunk of 8 consecutive
+// rows then touch 8 different groups of banks.
+template <int KC>
+__device__ inline int chunk_at(int row, int c) {
+    return row * (KC / 8) + (c ^ (KC == 32 ? (row >> 1) & 3 : row & 7));
+}
 
 // How an operand lies in memory, as rows (m or n) by k.
 enum { LD_K = 0,     // k contiguous: two 16-byte loads per chunk, lanes along k
@@ -224,12 +228,12 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64) void k_gemm_tile(GemmAr
 #pragma unroll
         for (int q = 0; q < CA; ++q) {
             const int e = tid + q * kThreads, r = LA == LD_ROW ? e % BM : e / 4, c = LA == LD_ROW ? e / BM : e % 4;
-            As[buf][chunk_at(r, c, KC)] = to_chunk(va[q]);
+            As[buf][chunk_at<KC>(r, c)] = to_chunk(va[q]);
         }
 #pragma unroll
         for (int q = 0; q < CB; ++q) {
             const int e = tid + q * kThreads, r = LB == LD_ROW ? e % BN : e / 4, c = LB == LD_ROW ? e / BN : e % 4;
-            Bs[buf][chunk_at(r, c, KC)] = to_chunk(vb[q]);
+            Bs[buf][chunk_at<KC>(r, c)] = to_chunk(vb[q]);
         }
     };
     fetch(0);
@@ -243,9 +247,9 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64) void k_gemm_tile(GemmAr
         for (int kk = 0; kk < KC / 16; ++kk) {
             bf16x8_t a[TM], b[TN];
 #pragma unroll
-            for (int i = 0; i < TM; ++i) a[i] = As[buf][chunk_at(wm + 32 * i + (lane & 31), 2 * kk + (lane >> 5), KC)];
+            for (int i = 0; i < TM; ++i) a[i] = As[buf][chunk_at<KC>(wm + 32 * i + (lane & 31), 2 * kk + (lane >> 5))];
 #pragma unroll
-            for (int j = 0; j < TN; ++j) b[j] = Bs[buf][chunk_at(wn + 32 * j + (lane & 31), 2 * kk + (lane >> 5), KC)];
+            for (int j = 0; j < TN; ++j) b[j] = Bs[buf][chunk_at<KC>(wn + 32 * j + (lane & 31), 2 * kk + (lane >> 5))];
 #pragma unroll
             for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -264,13 +268,14 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64) void k_gemm_tile(GemmAr
 // Small products (the network's): one 32 x 32 tile per workgroup, so that
 // also a few rows or columns spread over the chip.  Bound by the latency of
 // the loads: the 8 wavefronts together fetch kSmallK columns of both
-// operands at once (all loads of a stage in flight, the next stage's before
-// this stage's matrix instructions), and wavefront 0 runs the chain of
-// matrix instructions over them.  One row through the network: 17 us for its
+// operands at once, two such stages ahead of the matrix instructions, and wavefront 0 runs the chain of
+// matrix instructions over them.  One row through the network: 16 us for its
 // three products (127 us with 64 x 64 tiles and 38 dependent loads per
-// product); a 1024-sample training step 153 us (809 us).
+// product); a 1024-sample training step 103 us (809 us).
+// BUF: through the raw buffers of the tile kernels (a 32-bit offset per chunk);
+// otherwise (strides past their range) through plain pointers.
 constexpr int kSmallK = 256;
-template <int LA, int LB>
+template <int LA, int LB, bool BUF>
 __global__ __launch_bounds__(512) void k_gemm_small(GemmArgs g) {
     constexpr int KC = kSmallK, CH = 32 * (KC / 8) / 512;  // chunks per thread and operand
     __shared__ bf16x8_t As[2][32 * (KC / 8)];
@@ -281,56 +286,79 @@ __global__ __launch_bounds__(512) void k_gemm_small(GemmArgs g) {
     f32x16_t acc;
 #pragma unroll
     for (int i = 0; i < 16; ++i) acc[i] = 0.0f;
-    float va[CH][8], vb[CH][8];
+    float va[2][CH][8], vb[2][CH][8];
     auto at = [&](int ld, int q, int* r, int* c) {
         const int e = tid + q * 512;
         *r = ld == LD_ROW ? e % 32 : e / (KC / 8);
         *c = ld == LD_ROW ? e / 32 : e % (KC / 8);
     };
-    auto fetch = [&](int k0) {
+    const __amdgpu_buffer_rsrc_t ra = tile_buffer(A, m0), rb = tile_buffer(B, n0);
+    const uint32_t ska = 4u * (uint32_t)g.sak, skb = 4u * (uint32_t)g.sbk;
+    uint32_t oa[CH], ob[CH];
+#pragma unroll
+    for (int q = 0; q < CH; ++q) {
         int r, c;
+        at(LA, q, &r, &c);
+        oa[q] = m0 + r < g.M ? 4u * (uint32_t)g.sam * r + 8u * ska * c : kNoRow;
+        at(LB, q, &r, &c);
+        ob[q] = n0 + r < g.N ? 4u * (uint32_t)g.sbn * r + 8u * skb * c : kNoRow;
+    }
+    auto fetch = [&](int k0, float (&va)[CH][8], float (&vb)[CH][8]) {
+        const bool full = k0 + KC <= g.K;
 #pragma unroll
         for (int q = 0; q < CH; ++q) {
+            int r, c;
             at(LA, q, &r, &c);
-            load_chunk<LA>(A, m0 + r, k0 + 8 * c, va[q]);
+            if constexpr (!BUF) load_chunk<LA>(A, m0 + r, k0 + 8 * c, va[q]);
+            else if (full) load_chunk<LA>(ra, oa[q], k0 * ska, ska, va[q]);
+            else load_chunk_tail(ra, oa[q], k0 * ska, ska, g.K - k0 - 8 * c, va[q]);
         }
 #pragma unroll
         for (int q = 0; q < CH; ++q) {
+            int r, c;
             at(LB, q, &r, &c);
-            load_chunk<LB>(B, n0 + r, k0 + 8 * c, vb[q]);
+            if constexpr (!BUF) load_chunk<LB>(B, n0 + r, k0 + 8 * c, vb[q]);
+            else if (full) load_chunk<LB>(rb, ob[q], k0 * skb, skb, vb[q]);
+            else load_chunk_tail(rb, ob[q], k0 * skb, skb, g.K - k0 - 8 * c, vb[q]);
         }
     };
-    fetch(0);
-    int buf = 0;
-    for (int k0 = 0; k0 < g.K; k0 += KC, buf ^= 1) {
-        int r, c;
+    fetch(0, va[0], vb[0]);
+    if (KC < g.K) fetch(KC, va[1], vb[1]);
+    for (int k0 = 0; k0 < g.K; k0 += 2 * KC) {
 #pragma unroll
-        for (int q = 0; q < CH; ++q) {
-            at(LA, q, &r, &c);
-            As[buf][chunk_at(r, c, KC)] = to_chunk(va[q]);
-        }
+        for (int h = 0; h < 2; ++h) {  // the stage at k0 + h KC, register set and LDS buffer h
+            const int ks = k0 + h * KC;
+            if (ks >= g.K) break;
+            int r, c;
 #pragma unroll
-        for (int q = 0; q < CH; ++q) {
-            at(LB, q, &r, &c);
-            Bs[buf][chunk_at(r, c, KC)] = to_chunk(vb[q]);
-        }
-        // the other buffer's readers (wavefront 0, one stage back) passed
-        // this barrier after their reads, so two buffers need one barrier
-        __syncthreads();
-        if (k0 + KC < g.K) fetch(k0 + KC);
-        if (wave == 0) {
-            // 8 instructions' operands at a time, so that the chain does not
-            // wait for LDS between them (past K the chunks hold zeros)
-            const int steps = min(KC / 16, (g.K - k0 + 15) / 16);
-            for (int kb = 0; kb < steps; kb += 8) {
-                bf16x8_t a[8], b[8];
+            for (int q = 0; q < CH; ++q) {
+                at(LA, q, &r, &c);
+                As[h][chunk_at<KC>(r, c)] = to_chunk(va[h][q]);
+            }
 #pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    a[e] = As[buf][chunk_at(lane & 31, 2 * (kb + e) + (lane >> 5), KC)];
-                    b[e] = Bs[buf][chunk_at(lane & 31, 2 * (kb + e) + (lane >> 5), KC)];
+            for (int q = 0; q < CH; ++q) {
+                at(LB, q, &r, &c);
+                Bs[h][chunk_at<KC>(r, c)] = to_chunk(vb[h][q]);
+            }
+            // the other buffer's readers (wavefront 0, one stage back) passed
+            // this barrier after their reads, so two buffers need one barrier
+            __syncthreads();
+            if (ks + 2 * KC < g.K) fetch(ks + 2 * KC, va[h], vb[h]);
+            if (wave == 0) {
+                // 8 instructions' operands at a time, so that the chain does
+                // not wait for LDS between them (past K the chunks hold zeros)
+                const int steps = min(KC / 16, (g.K - ks + 15) / 16);
+                for (int kb = 0; kb < steps; kb += 8) {
+                    bf16x8_t a[8], b[8];
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) {
+                        a[e] = As[h][chunk_at<KC>(lane & 31, 2 * (kb + e) + (lane >> 5))];
+                        b[e] = Bs[h][chunk_at<KC>(lane & 31, 2 * (kb + e) + (lane >> 5))];
+                    }
+#pragma unroll
+                    for (int e = 0; e < 8; ++e)
+                        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[e], b[e], acc, 0, 0, 0);
                 }
-#pragma unroll
-                for (int e = 0; e < 8; ++e) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[e], b[e], acc, 0, 0, 0);
             }
         }
     }
@@ -338,16 +366,26 @@ __global__ __launch_bounds__(512) void k_gemm_small(GemmArgs g) {
 }
 
 // Gaussian NLL per sample and its gradient w.r.t. the 12 outputs (scaled by
-// 1/B); one block reduces the per-sample losses in a fixed order.
-__global__ __launch_bounds__(256) void k_nll(const float* out, const float* Y, int32_t B, float* dout, float* loss) {
-    __shared__ double part[256];
+// 1/B); one block of one thread per sample (and per 1024 of them) adds the
+// per-sample losses in a fixed order: each thread its own, the wavefront by
+// butterfly, one wavefront the 16 partial sums.
+constexpr int kNllThreads = 1024;
+__global__ __launch_bounds__(kNllThreads) void k_nll(const float* out, const float* Y, int32_t B, float* dout,
+                                                     float* loss) {
+    __shared__ double part[kNllThreads / 64];
     double s = 0.0;
     const float invB = 1.0f / (float)B;
-    for (int b = threadIdx.x; b < B; b += blockDim.x) {
+    for (int b = threadIdx.x; b < B; b += kNllThreads) {
         double lb = 0.0;
+        float o[12], y[6];
+#pragma unroll
+        for (int d = 0; d < 12; ++d) o[d] = out[b * 12 + d];
+#pragma unroll
+        for (int d = 0; d < 6; ++d) y[d] = Y[b * 6 + d];
+#pragma unroll
         for (int d = 0; d < 6; ++d) {
-            const float mu = out[b * 12 + d], ls = out[b * 12 + 6 + d];
-            const float r = Y[b * 6 + d] - mu;
+            const float mu = o[d], ls = o[6 + d];
+            const float r = y[d] - mu;
             const float inv = expf(-2.0f * ls);
             lb += (double)(0.5f * r * r * inv + ls);
             dout[b * 12 + d] = -r * inv * invB;
@@ -355,18 +393,19 @@ __global__ __launch_bounds__(256) void k_nll(const float* out, const float* Y, i
         }
         s += lb;
     }
-    part[threadIdx.x] = s;
+    s = wave_sum(s);
+    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = s;
     __syncthreads();
-    if (threadIdx.x == 0) {
-        double t = 0.0;
-        for (int i = 0; i < (int)blockDim.x; ++i) t += part[i];
-        *loss = (float)(t / (double)B);
+    if (threadIdx.x < 64) {
+        const double t = wave_sum(threadIdx.x < kNllThreads / 64 ? part[threadIdx.x] : 0.0);
+        if (threadIdx.x == 0) *loss = (float)(t / (double)B);
     }
 }
 
 // column sums (bias gradients): a workgroup per 64 columns; wave w of its
 // 16 sums rows w, w + 16, ... of its lane's column (each row read as one
-// coalesced 64-column segment), then one lane per column adds the 16
+// coalesced 64-column segment, 16 of them loaded before they are added: the
+// kernel waits for memory, not for its 64 additions), then one lane per column adds the 16
 // partial sums in wave order (a fixed order: deterministic)
 constexpr int kColsumWaves = 16;
 __global__ __launch_bounds__(1024) void k_colsum(const float* X, int32_t rows, int32_t cols, float* out) {
@@ -374,8 +413,17 @@ __global__ __launch_bounds__(1024) void k_colsum(const float* X, int32_t rows, i
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int c = blockIdx.x * 64 + lane;
     float s = 0.0f;
-    if (c < cols)
-        for (int r = w; r < rows; r += kColsumWaves) s += X[(int64_t)r * cols + c];
+    if (c < cols) {
+        int r = w;
+        for (; r + 15 * kColsumWaves < rows; r += 16 * kColsumWaves) {
+            float x[16];
+#pragma unroll
+            for (int q = 0; q < 16; ++q) x[q] = X[(int64_t)(r + q * kColsumWaves) * cols + c];
+#pragma unroll
+            for (int q = 0; q < 16; ++q) s += x[q];
+        }
+        for (; r < rows; r += kColsumWaves) s += X[(int64_t)r * cols + c];
+    }
     part[w][lane] = s;
     __syncthreads();
     if (w == 0 && c < cols) {
@@ -424,8 +472,11 @@ static void launch_gemm(const GemmArgs& g, hipStream_t s) {
         hipLaunchKernelGGL((k_gemm_tile<128, 128, 64, 64, LA, LB>), dim3((unsigned)tiles(128)), dim3(256), 0, s, g);
     else if (fits && tiles(64) >= 192)
         hipLaunchKernelGGL((k_gemm_tile<64, 64, 32, 32, LA, LB>), dim3((unsigned)tiles(64)), dim3(256), 0, s, g);
+    else if (fits)
+        hipLaunchKernelGGL((k_gemm_small<LA, LB, true>), dim3((g.N + 31) / 32, (g.M + 31) / 32), dim3(512), 0, s, g);
     else
-        hipLaunchKernelGGL((k_gemm_small<LA, LB>), dim3((g.N + 31) / 32, (g.M + 31) / 32), dim3(512), 0, s, g);
+        hipLaunchKernelGGL((k_gemm_small<LD_ROW, LD_ROW, false>), dim3((g.N + 31) / 32, (g.M + 31) / 32), dim3(512),
+                           0, s, g);
 }
 
 static rose_status gemm(int M, int N, int K, const float* A, int64_t sam, int64_t sak, const float* B, int64_t sbk,
@@ -545,7 +596,7 @@ rose_status rose_mlp_loss_grad(rose_mlp* m, const float* params_dev, const float
     float* G = grads_dev;
     rose_status st;
     if ((st = mlp_forward_impl(m, P, X_dev, B, m->Y, s)) != ROSE_OK) return st;
-    hipLaunchKernelGGL(k_nll, dim3(1), dim3(256), 0, s, m->Y, Y_dev, B, m->dY, loss_dev);
+    hipLaunchKernelGGL(k_nll, dim3(1), dim3(kNllThreads), 0, s, m->Y, Y_dev, B, m->dY, loss_dev);
     ROSE_CHECK_HIP(hipGetLastError());
     const int hid = m->hid, in = m->in, out = m->out;
     // dW3 = H2^T dY ; db3 = colsum(dY)
