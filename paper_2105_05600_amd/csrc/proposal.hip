@@ -40,52 +40,219 @@ struct RaycastArgs {
     float* out;
 };
 
-// One wavefront per pixel: the fixed-step march of the ray is evaluated 64
-// samples at a time, lane j taking sample k = base + j (z = near + k step,
-// the same expression as a serial march, so the samples are identical).  A
-// crossing at k is a + to - change between samples k-1 and k inside the
-// truncation band; sample k-1 comes from the lane below (lane 0 keeps the
-// previous chunk's last sample).  The first crossing in step order -- the
-// lowest lane of the first chunk that has one -- gives the depth by linear
-// interpolation, exactly as a serial march stopping there would.
+// Sample k of a ray, as a serial march computes it.
 template <int FMT>
+__device__ inline double ray_sample(const RaycastArgs& a, const double dw[3], double z) {
+    const double vox = (double)a.g.vox;
+    double h[3];
+    for (int c = 0; c < 3; ++c) h[c] = (a.t[c] + z * dw[c] - (double)a.g.origin[c]) / vox - 0.5;
+    return trilinear64<FMT>(a.g, h[0], h[1], h[2]);
+}
+
+// Whether a sample of a ray may be <= 0: no, when it is outside the grid (+1)
+// or all 8 corners are > 0 (the interpolation weights are >= 0 and not all
+// 0); yes (the sample is then evaluated), when a corner is <= 0 or NaN, or
+// its voxel coordinates are so close to a voxel or grid boundary that the
+// corners are not certain.  The coordinates are i0 + f with the voxel i0 of a
+// stretch's first sample and f = f0 + d b in binary32 (d below 128, |b| at
+// most 8 voxels: within 1e-4 of ray_sample's).  Loads are unconditional
+// (voxel 0 for the lanes that do not need theirs), so that those of several
+// samples are in flight together.
+struct RayTest {
+    float v[8];
+    bool outside, unsure;
+};
+
+// sign-exact value of a 16-bit voxel
+template <int FMT>
+__device__ inline float psi_of_bits(unsigned short b) {
+    if constexpr (FMT == ROSE_TSDF_F16) return __half2float(__ushort_as_half(b));
+    else return (float)(int16_t)b;
+}
+
+template <int FMT, bool WIDE>
+__device__ inline void ray_test_load(const Grid& g, __amdgpu_buffer_rsrc_t psi, const int i0[3], const float f0[3],
+                                     const float fb[3], float d, RayTest& t) {
+    constexpr float kEps = 1e-4f;
+    const int32_t n[3] = {g.nx, g.ny, g.nz};
+    uint32_t i[3];
+    t.outside = false;
+    t.unsure = false;
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        const float f = fmaf(d, fb[c], f0[c]), fl = floorf(f), fr = f - fl;
+        const int h = i0[c] + (int)fl;
+        const bool in = (uint32_t)h < (uint32_t)(n[c] - 1);
+        t.outside = t.outside || !in;
+        t.unsure = t.unsure || fr < kEps || fr > 1.0f - kEps;
+        i[c] = in ? (uint32_t)h : 0u;
+    }
+    const uint32_t x[2] = {(i[0] & ~7u) * 63u + i[0], ((i[0] + 1) & ~7u) * 63u + i[0] + 1};
+    const uint32_t y[2] = {__umul24(i[1] & ~7u, (uint32_t)g.bstride_y) + 8 * i[1],
+                           __umul24((i[1] + 1) & ~7u, (uint32_t)g.bstride_y) + 8 * (i[1] + 1)};
+    const uint32_t z[2] = {__umul24(i[2] & ~7u, (uint32_t)g.bstride_z) + 64 * i[2],
+                           __umul24((i[2] + 1) & ~7u, (uint32_t)g.bstride_z) + 64 * (i[2] + 1)};
+    if constexpr (WIDE) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) t.v[e] = load_psi<FMT>(g.psi, x[e & 1] + y[(e >> 1) & 1] + z[e >> 2]);
+        return;
+    }
+    // the two x neighbours of a corner row in one load, except across a brick
+    // boundary (the lanes with i mod 8 = 7 load the second apart): gathers
+    // are what the march waits for
+    const bool split = (i[0] & 7u) == 7u;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const uint32_t off = x[0] + y[e & 1] + z[e >> 1];
+        if constexpr (FMT == ROSE_TSDF_F32) {
+            const auto w = __builtin_amdgcn_raw_buffer_load_b64(psi, (int)(4u * off), 0, 0);
+            t.v[2 * e] = __uint_as_float(w[0]);
+            t.v[2 * e + 1] = __uint_as_float(w[1]);
+        } else {  // the 4 values from the 4-byte boundary at or below
+            const auto w = __builtin_amdgcn_raw_buffer_load_b64(psi, (int)(2u * (off & ~1u)), 0, 0);
+            const uint32_t pair = __builtin_amdgcn_alignbit(w[1], w[0], 16u * (off & 1u));
+            t.v[2 * e] = psi_of_bits<FMT>((unsigned short)pair);
+            t.v[2 * e + 1] = psi_of_bits<FMT>((unsigned short)(pair >> 16));
+        }
+    }
+    if (split) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const uint32_t off = x[1] + y[e & 1] + z[e >> 1];
+            if constexpr (FMT == ROSE_TSDF_F32)
+                t.v[2 * e + 1] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(psi, (int)(4u * off), 0, 0));
+            else
+                t.v[2 * e + 1] = psi_of_bits<FMT>(__builtin_amdgcn_raw_buffer_load_b16(psi, (int)(2u * off), 0, 0));
+        }
+    }
+}
+
+__device__ inline bool ray_test(const RayTest& t) {
+    bool pos = true;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) pos = pos && t.v[e] > 0.0f;
+    return t.unsure || (!t.outside && !pos);
+}
+
+// The fixed-step march of the rays: a wavefront takes a TP x TP patch of
+// pixels and NS = 64 / TP^2 consecutive samples of each (z = near + k step,
+// the same expression as a serial march, so the samples are identical), U
+// such groups in flight together.  A crossing at k is a + to - change
+// between samples k-1 and k inside the truncation band, so only a sample
+// that may be <= 0 and the one before it need a value: the others (free
+// space, the bulk of every ray) are told by ray_test.  The first crossing in
+// step order gives the depth by linear interpolation, exactly as a serial
+// march stopping there would.  Bound by the gathers' cache-line lookups (8
+// corners per sample in 4 loads; with one load per corner 258 us at 320 x
+// 240, whatever the arithmetic around them).
+template <int FMT, bool WIDE, int TP, int U>
 __global__ __launch_bounds__(256) void k_raycast(RaycastArgs a) {
-    const int lane = threadIdx.x & 63;
-    const int64_t idx = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (idx >= (int64_t)a.W * a.H) return;  // whole wavefronts leave together
-    const int u = (int)(idx % a.W), v = (int)(idx / a.W);
+    constexpr int NS = kWave / (TP * TP);
+    const int lane = threadIdx.x & 63, px = lane / NS, j = lane % NS;
+    const int tiles_x = (a.W + TP - 1) / TP, tiles_y = (a.H + TP - 1) / TP;
+    const int tile = blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (tile >= tiles_x * tiles_y) return;  // whole wavefronts leave together
+    const int u = (tile % tiles_x) * TP + px % TP, v = (tile / tiles_x) * TP + px / TP;
     const double dc[3] = {((double)u - a.cx) / a.fx, ((double)v - a.cy) / a.fy, 1.0};
     double dw[3];
     for (int i = 0; i < 3; ++i) dw[i] = a.R[3 * i + 0] * dc[0] + a.R[3 * i + 1] * dc[1] + a.R[3 * i + 2] * dc[2];
-    const double vox = (double)a.g.vox;
-    double carry = 0.0;  // sample base - 1 (from the previous chunk)
-    double out = 0.0;
-    for (int64_t base = 0;; base += kWave) {
-        const int64_t k = base + lane;
-        const double z = a.near_z + (double)k * a.step;
-        const bool valid = !(z > a.far_z);
-        double s = 0.0;
-        if (valid) {
-            double h[3];
-            for (int c = 0; c < 3; ++c) h[c] = (a.t[c] + z * dw[c] - (double)a.g.origin[c]) / vox - 0.5;
-            s = trilinear64<FMT>(a.g, h[0], h[1], h[2]);
-        }
-        double prev = __shfl_up(s, 1, kWave);
-        if (lane == 0) prev = carry;
-        const bool cross = valid && k >= 1 && prev > 0.0 && s <= 0.0 && prev < 1.0 && s > -1.0;
-        const uint64_t hits = __ballot(cross);
-        if (hits) {
-            const int first = __ffsll((unsigned long long)hits) - 1;
-            const double zp = a.near_z + (double)(k - 1) * a.step;
-            const double o = zp + a.step * prev / (prev - s);
-            out = __shfl(o, first, kWave);
-            break;
-        }
-        // any lane past `far` ends the march (later chunks are all past it)
-        if (__ballot(!valid)) break;
-        carry = __shfl(s, kWave - 1, kWave);
+    const uint32_t bytes = (uint32_t)a.g.nx * (uint32_t)a.g.ny * (uint32_t)a.g.nz * (FMT == ROSE_TSDF_F32 ? 4u : 2u);
+    const __amdgpu_buffer_rsrc_t psi = __builtin_amdgcn_make_buffer_rsrc(a.g.psi, (short)0, (int)bytes, 0x00020000);
+    // voxel coordinates ha + k hb; where they are too large or too far apart
+    // for ray_test's margin, every sample is evaluated
+    double ha[3], hb[3];
+    float fb[3];
+    bool plain = false;
+    const double inv = 1.0 / (double)a.g.vox, kmax = (a.far_z - a.near_z) / a.step + 2.0;
+    for (int c = 0; c < 3; ++c) {
+        ha[c] = (a.t[c] + a.near_z * dw[c] - (double)a.g.origin[c]) * inv - 0.5;
+        hb[c] = a.step * dw[c] * inv;
+        fb[c] = (float)hb[c];
+        plain = plain || !((fabs(a.t[c]) + fabs((double)a.g.origin[c])) * inv + kmax * fabs(hb[c]) +
+                               fabs(a.near_z * dw[c]) * inv < 1e8) || !(fabs(hb[c]) <= 8.0);
     }
-    if (lane == 0) a.out[idx] = (float)out;
+    // samples before the ray enters the grid and after it leaves it are +1
+    double k0 = 0.0, k1 = kmax;
+    if (!plain) {
+        const int32_t n[3] = {a.g.nx, a.g.ny, a.g.nz};
+        for (int c = 0; c < 3; ++c) {
+            const double e0 = (-1e-3 - ha[c]) / hb[c], e1 = ((double)(n[c] - 1) + 1e-3 - ha[c]) / hb[c];
+            if (hb[c] > 0.0) {
+                k0 = fmax(k0, e0);
+                k1 = fmin(k1, e1);
+            } else if (hb[c] < 0.0) {
+                k0 = fmax(k0, e1);
+                k1 = fmin(k1, e0);
+            }
+        }
+    }
+    const int kend = (int)fmin(fmax(k1 + 2.0, 0.0), kmax);
+    int base = (int)fmin(fmax(k0 - 2.0, 0.0), kmax);
+    double out = 0.0;
+    bool done = u >= a.W || v >= a.H || base > kend;
+    for (; !done; base += U * NS, done = done || base > kend) {
+        int i0[3];
+        float f0[3];
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            const double h = fma((double)base, hb[c], ha[c]), fl = floor(fmin(fmax(h, -1e8), 1e8));
+            i0[c] = (int)fl;
+            f0[c] = (float)(h - fl);
+        }
+        RayTest t[U];
+#pragma unroll
+        for (int q = 0; q < U; ++q) ray_test_load<FMT, WIDE>(a.g, psi, i0, f0, fb, (float)(q * NS + j), t[q]);
+#pragma unroll
+        for (int q = 0; q < U; ++q) {
+            if (done) break;
+            const int k = base + q * NS + j;
+            const double z = a.near_z + (double)k * a.step;
+            const bool valid = !(z > a.far_z);
+            double prev = 0.0, s = 1.0;
+            bool cross = false;
+            if (valid && k >= 1 && (plain || ray_test(t[q]))) {
+                s = ray_sample<FMT>(a, dw, z);
+                if (s <= 0.0 && s > -1.0) {
+                    prev = ray_sample<FMT>(a, dw, a.near_z + (double)(k - 1) * a.step);
+                    cross = prev > 0.0 && prev < 1.0;
+                }
+            }
+            // the pixel's lanes leave the loop together: they are all active here
+            const uint64_t hits = (__ballot(cross) >> (px * NS)) & (NS == 64 ? ~0ull : (1ull << (NS & 63)) - 1ull);
+            if (hits) {
+                const int first = __ffsll((unsigned long long)hits) - 1;
+                const double zp = a.near_z + (double)(k - 1) * a.step;
+                const double o = zp + a.step * prev / (prev - s);
+                out = __shfl(o, px * NS + first, kWave);
+                done = true;
+            }
+        }
+    }
+    if (j == 0 && u < a.W && v < a.H) a.out[(int64_t)v * a.W + u] = (float)out;
+}
+
+template <int FMT, bool WIDE>
+static void launch_raycast(const RaycastArgs& a, hipStream_t s) {
+    auto blocks = [&](int tp) { return dim3((unsigned)((((a.W + tp - 1) / tp) * ((a.H + tp - 1) / tp) + 3) / 4)); };
+    // A patch of neighbouring rays shares lines that the samples along one ray
+    // do not, but leaves fewer wavefronts, whose rounds follow one another
+    // (512^3 at 1 cm, half-voxel steps, us with 1 / 4 / 16 pixels per
+    // wavefront): 80 x 60 19 / 33 / 110, 160 x 120 56 / 50 / 114, 320 x 240
+    // 190 / 139 / 151, 640 x 480 728 / 481 / 436; 239 and 904 us at the last
+    // two sizes with every sample evaluated.
+    const int64_t pixels = (int64_t)a.W * a.H;
+    if (pixels < 15000) hipLaunchKernelGGL((k_raycast<FMT, WIDE, 1, 2>), blocks(1), dim3(256), 0, s, a);
+    else if (pixels < (1 << 18)) hipLaunchKernelGGL((k_raycast<FMT, WIDE, 2, 2>), blocks(2), dim3(256), 0, s, a);
+    else hipLaunchKernelGGL((k_raycast<FMT, WIDE, 4, 2>), blocks(4), dim3(256), 0, s, a);
+}
+
+template <int FMT>
+static void launch_raycast_fmt(const RaycastArgs& a, hipStream_t s) {
+    const uint64_t bytes = (uint64_t)a.g.nx * a.g.ny * a.g.nz * (FMT == ROSE_TSDF_F32 ? 4u : 2u);
+    // plain pointers for volumes past 32-bit offsets, and for a 16-bit buffer
+    // that is not aligned to the pairs the buffer loads take
+    if (bytes >= (uint64_t(1) << 32) || ((uintptr_t)a.g.psi & 3u)) launch_raycast<FMT, true>(a, s);
+    else launch_raycast<FMT, false>(a, s);
 }
 
 struct FeatureArgs {
@@ -141,10 +308,9 @@ rose_status tsdf_raycast(const rose_tsdf* h, const rose_pose* T_wc, const rose_c
     a.fx = cam->fx; a.fy = cam->fy; a.cx = cam->cx; a.cy = cam->cy;
     a.near_z = near_m; a.far_z = far_m; a.step = step_m;
     a.out = depth_out_dev;
-    const unsigned blocks = (unsigned)((a.W * a.H + 3) / 4);  // 4 pixels (wavefronts) per workgroup
-    if (h->g.fmt == ROSE_TSDF_F32) hipLaunchKernelGGL(k_raycast<ROSE_TSDF_F32>, dim3(blocks), dim3(256), 0, s, a);
-    else if (h->g.fmt == ROSE_TSDF_F16) hipLaunchKernelGGL(k_raycast<ROSE_TSDF_F16>, dim3(blocks), dim3(256), 0, s, a);
-    else hipLaunchKernelGGL(k_raycast<ROSE_TSDF_SN16>, dim3(blocks), dim3(256), 0, s, a);
+    if (h->g.fmt == ROSE_TSDF_F32) launch_raycast_fmt<ROSE_TSDF_F32>(a, s);
+    else if (h->g.fmt == ROSE_TSDF_F16) launch_raycast_fmt<ROSE_TSDF_F16>(a, s);
+    else launch_raycast_fmt<ROSE_TSDF_SN16>(a, s);
     ROSE_CHECK_HIP(hipGetLastError());
     return ROSE_OK;
 }
