@@ -435,6 +435,7 @@ struct FitLaunch {
     int32_t pl_side;
     float pl_thr;   // voxels
     float pl_zref;  // metres: depth at which a rotation axis length is turned into a displacement
+    int32_t ones_lds;          // 1: points-across workgroups stage the brick bits in LDS (set by the launch)
     uint64_t* partial;         // n x splits x kPartSub grid integers (partial_index)
 };
 
@@ -476,10 +477,12 @@ FitConfig fit_config(const rose_tsdf* h);
 void fit_launch_shape(const rose_tsdf* h, int lk, int* p, int* u, float* thr_vox, float* zref_m);
 int fitness_blocks(const FitLaunch& L, int P);
 bool batch_shape_valid(int p, int u);
-int batch_grid(int P, int U, int fmt, int lk, int requested);
+int batch_grid(int P, int U, int fmt, int lk, int requested, int lds);
+// LDS bytes that a points-across launch of shape P takes for a volume's brick bits (0: none)
+int ones_lds_bytes(const Grid& g, int lk, int P);
 // ctr_dev: the group's 8 per-XCD work counters, zero at launch
 rose_status launch_fitness_batch(const FitLaunch* seqs_dev, const int* begin_dev, int count, int base, int end,
-                                 int grid, int P, int U, int fmt, int lk, int* ctr_dev, hipStream_t s);
+                                 int grid, int lds, int P, int U, int fmt, int lk, int* ctr_dev, hipStream_t s);
 
 // PST template rows 0..n-1 (tsdf.hip)
 rose_status launch_pst_sample(int64_t n, uint64_t seed, float* out_dev, hipStream_t s);

@@ -34,6 +34,8 @@ __device__ inline uint32_t elem_bytes() {
 struct PsiBuf {
     __amdgpu_buffer_rsrc_t r;
     __amdgpu_buffer_rsrc_t ones;
+    __amdgpu_buffer_rsrc_t pair;  // 16-bit formats: psi from the 4-byte boundary at or below it,
+    uint32_t mis;                 // and its offset from there
 };
 
 template <int FMT>
@@ -41,8 +43,11 @@ __device__ inline PsiBuf psi_buffer(const Grid& g) {
     const uint32_t bytes = (uint32_t)g.nx * (uint32_t)g.ny * (uint32_t)g.nz * elem_bytes<FMT>();
     const uint32_t words = ((uint32_t)g.nbx * (uint32_t)g.nby * (uint32_t)g.nbz + 31u) / 32u;
     // dword 3 of a raw (stride 0) buffer resource on gfx9-family targets
+    const uint32_t mis = (uint32_t)(uintptr_t)g.psi & 3u;
     return PsiBuf{__builtin_amdgcn_make_buffer_rsrc(g.psi, (short)0, (int)bytes, 0x00020000),
-                  __builtin_amdgcn_make_buffer_rsrc(g.ones, (short)0, (int)(4u * words), 0x00020000)};
+                  __builtin_amdgcn_make_buffer_rsrc(g.ones, (short)0, (int)(4u * words), 0x00020000),
+                  __builtin_amdgcn_make_buffer_rsrc((char*)g.psi - mis, (short)0, (int)(bytes + mis), 0x00020000),
+                  mis};
 }
 
 // whether the brick holding the voxel at element offset `off` is all +1
@@ -51,6 +56,19 @@ __device__ inline PsiBuf psi_buffer(const Grid& g) {
 __device__ inline bool brick_all_ones(const PsiBuf& b, uint32_t off) {
     const uint32_t w = __builtin_amdgcn_raw_buffer_load_b32(b.ones, (int)((off >> 12) & ~3u), 0, 0);
     return __builtin_amdgcn_ubfe(w, off >> 9, 1) != 0u;
+}
+
+// The brick bits of volumes up to 512^3 (kOnesLdsWords words) are staged in
+// LDS by the points-across kernels: read through the vector memory path the
+// word of an evaluation costs as much of its cache-access rate as 16 of the
+// gather's lines (a quarter of all accesses on the wide search), and that rate
+// is what bounds the kernel (its data return busy 99 % of the time).  512^3,
+// 10240 particles x 19200 points, axis lengths 0.005 / 0.05 / 0.15: 366 / 409 /
+// 355 us -> 287 / 385 / 330; the bench's points-across steps 0.632 -> 0.598 ms.
+constexpr uint32_t kOnesLdsWords = 8192;  // 32 KB
+
+__host__ __device__ inline uint32_t ones_words(const Grid& g) {
+    return ((uint32_t)g.nbx * (uint32_t)g.nby * (uint32_t)g.nbz + 31u) / 32u;
 }
 
 template <int FMT, bool WIDE>
@@ -66,6 +84,18 @@ __device__ inline float gather(const Grid& g, const PsiBuf& b, uint32_t off) {
         } else {
             return (float)(int16_t)__builtin_amdgcn_raw_buffer_load_b16(b.r, bo, 0, 0) * (1.0f / 32767.0f);
         }
+    }
+}
+
+// psi at a byte offset of a voxel inside the volume
+template <int FMT>
+__device__ inline float gather_bytes(const PsiBuf& b, uint32_t bo) {
+    if constexpr (FMT == ROSE_TSDF_F32) {
+        return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(b.r, (int)bo, 0, 0));
+    } else if constexpr (FMT == ROSE_TSDF_F16) {
+        return __half2float(__ushort_as_half(__builtin_amdgcn_raw_buffer_load_b16(b.r, (int)bo, 0, 0)));
+    } else {
+        return (float)(int16_t)__builtin_amdgcn_raw_buffer_load_b16(b.r, (int)bo, 0, 0) * (1.0f / 32767.0f);
     }
 }
 
@@ -119,29 +149,77 @@ __device__ inline bool nearest_offset(const Grid& g, const VoxelTest& e, float g
     return in;
 }
 
+// TRILINEAR: the cell of a voxel-space coordinate, its weights and its 8
+// corner values.  Bound by the accesses that its gathers make (one per
+// distinct line of 4 lanes), so:  The two x neighbours of a corner row are contiguous in
+// memory except across a brick boundary, so a cell is 4 loads of a pair each;
+// the lanes with i mod 8 = 7 load the second value of each pair apart, in 4
+// more loads that the other lanes aim past the buffer's end, where they fetch
+// no line.  384 x 392 x 248 binary16, 4096 particles x 4800 points, 20
+// iterations: 2735 -> 2140 us; 512^3 binary32, 10240 x 19200: 2310 -> 1660
+// us.  The 16-bit formats read the 4 values from the 4-byte boundary at
+// or below the first one (mis: the buffer's own offset from such a boundary).
+struct TriCell {
+    float fx, fy, fz;
+    bool in, split;
+    float v[8], w[4];  // corners (the second of each pair for lanes without a split), their replacements
+};
+
+template <int FMT>
+__device__ inline float psi_of_bits(uint32_t b) {
+    if constexpr (FMT == ROSE_TSDF_F16) return __half2float(__ushort_as_half((unsigned short)b));
+    else return (float)(int16_t)b * (1.0f / 32767.0f);
+}
+
 template <int FMT, bool WIDE>
-__device__ inline float lookup_trilinear(const Grid& g, const PsiBuf& b, float gx, float gy, float gz) {
+__device__ inline void tri_load(const Grid& g, const PsiBuf& b, float gx, float gy, float gz, TriCell& c) {
     const float hx = gx - 0.5f, hy = gy - 0.5f, hz = gz - 0.5f;
-    const bool in = (hx >= 0.0f) & (hx < (float)(g.nx - 1)) & (hy >= 0.0f) & (hy < (float)(g.ny - 1)) &
-                    (hz >= 0.0f) & (hz < (float)(g.nz - 1));
-    const uint32_t ix = in ? (uint32_t)hx : 0u, iy = in ? (uint32_t)hy : 0u, iz = in ? (uint32_t)hz : 0u;
-    const float fx = hx - (float)ix, fy = hy - (float)iy, fz = hz - (float)iz;
-    const float v000 = gather<FMT, WIDE>(g, b, brick_offset(g, ix, iy, iz));
-    const float v100 = gather<FMT, WIDE>(g, b, brick_offset(g, ix + 1, iy, iz));
-    const float v010 = gather<FMT, WIDE>(g, b, brick_offset(g, ix, iy + 1, iz));
-    const float v110 = gather<FMT, WIDE>(g, b, brick_offset(g, ix + 1, iy + 1, iz));
-    const float v001 = gather<FMT, WIDE>(g, b, brick_offset(g, ix, iy, iz + 1));
-    const float v101 = gather<FMT, WIDE>(g, b, brick_offset(g, ix + 1, iy, iz + 1));
-    const float v011 = gather<FMT, WIDE>(g, b, brick_offset(g, ix, iy + 1, iz + 1));
-    const float v111 = gather<FMT, WIDE>(g, b, brick_offset(g, ix + 1, iy + 1, iz + 1));
-    const float c00 = fmaf(fx, v100 - v000, v000);
-    const float c10 = fmaf(fx, v110 - v010, v010);
-    const float c01 = fmaf(fx, v101 - v001, v001);
-    const float c11 = fmaf(fx, v111 - v011, v011);
-    const float c0 = fmaf(fy, c10 - c00, c00);
-    const float c1 = fmaf(fy, c11 - c01, c01);
-    const float v = fmaf(fz, c1 - c0, c0);
-    return in ? v : 1.0f;
+    c.in = (hx >= 0.0f) & (hx < (float)(g.nx - 1)) & (hy >= 0.0f) & (hy < (float)(g.ny - 1)) & (hz >= 0.0f) &
+           (hz < (float)(g.nz - 1));
+    const uint32_t ix = c.in ? (uint32_t)hx : 0u, iy = c.in ? (uint32_t)hy : 0u, iz = c.in ? (uint32_t)hz : 0u;
+    c.fx = hx - (float)ix;
+    c.fy = hy - (float)iy;
+    c.fz = hz - (float)iz;
+    c.split = (ix & 7u) == 7u;
+    // steps to the next row and layer: within the brick, or to the next one
+    const uint32_t dy = (iy & 7u) == 7u ? 512u * (uint32_t)g.nbx - 56u : 8u;
+    const uint32_t dz = (iz & 7u) == 7u ? 512u * (uint32_t)g.nbx * (uint32_t)g.nby - 448u : 64u;
+    const uint32_t o = brick_offset(g, ix, iy, iz);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const uint32_t row = o + ((e & 1) ? dy : 0u) + ((e >> 1) ? dz : 0u);
+        if constexpr (WIDE) {
+            c.v[2 * e] = load_psi<FMT>(g.psi, row);
+            c.v[2 * e + 1] = load_psi<FMT>(g.psi, row + (c.split ? 505u : 1u));
+            c.w[e] = c.v[2 * e + 1];
+        } else {
+            if constexpr (FMT == ROSE_TSDF_F32) {
+                const auto p = __builtin_amdgcn_raw_buffer_load_b64(b.r, (int)(4u * row), 0, 0);
+                c.v[2 * e] = __uint_as_float(p[0]);
+                c.v[2 * e + 1] = __uint_as_float(p[1]);
+            } else {
+                const uint32_t bo = 2u * row + b.mis;
+                const auto q = __builtin_amdgcn_raw_buffer_load_b64(b.pair, (int)(bo & ~3u), 0, 0);
+                const uint32_t p = __builtin_amdgcn_alignbit(q[1], q[0], 8u * (bo & 2u));
+                c.v[2 * e] = psi_of_bits<FMT>(p & 0xffffu);
+                c.v[2 * e + 1] = psi_of_bits<FMT>(p >> 16);
+            }
+            c.w[e] = gather_bytes<FMT>(b, c.split ? elem_bytes<FMT>() * (row + 505u) : 0xfffffffcu);
+        }
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) c.v[2 * e + 1] = c.split ? c.w[e] : c.v[2 * e + 1];
+}
+
+__device__ inline float tri_value(const TriCell& c) {
+    const float c00 = fmaf(c.fx, c.v[1] - c.v[0], c.v[0]);
+    const float c10 = fmaf(c.fx, c.v[3] - c.v[2], c.v[2]);
+    const float c01 = fmaf(c.fx, c.v[5] - c.v[4], c.v[4]);
+    const float c11 = fmaf(c.fx, c.v[7] - c.v[6], c.v[6]);
+    const float c0 = fmaf(c.fy, c10 - c00, c00);
+    const float c1 = fmaf(c.fy, c11 - c01, c01);
+    const float v = fmaf(c.fz, c1 - c0, c0);
+    return c.in ? v : 1.0f;
 }
 
 __device__ inline float bcast(float v, int lane) {
@@ -191,8 +269,18 @@ __device__ inline void psi_batch(const Grid& g, const PsiBuf& b, const VoxelTest
             asm("" : "+v"(v[k]));
         }
     } else {
+        // evaluations in flight together: 4, or 2 with the 16-bit formats,
+        // whose pairs take more registers until they are decoded
+        constexpr int kMost = FMT == ROSE_TSDF_F32 ? 4 : 2, kB = K < kMost ? K : kMost;
 #pragma unroll
-        for (int k = 0; k < K; ++k) v[k] = lookup_trilinear<FMT, WIDE>(g, b, gx[k], gy[k], gz[k]);
+        for (int k0 = 0; k0 < K; k0 += kB) {
+            TriCell c[kB];
+#pragma unroll
+            for (int k = 0; k < kB; ++k) tri_load<FMT, WIDE>(g, b, gx[k0 + k], gy[k0 + k], gz[k0 + k], c[k]);
+#pragma unroll
+            for (int k = 0; k < kB; ++k) v[k0 + k] = tri_value(c[k]);
+            __builtin_amdgcn_sched_barrier(0);  // keeps the next ones' loads out of this one's registers
+        }
     }
 }
 
@@ -208,8 +296,11 @@ __device__ inline void add_sq(uint64_t& acc, float& accf, float v) {
 // a binary32 sum (no-Kahan ablation) as a grid integer
 __device__ inline uint64_t grid_of_f32_sum(float f) { return (uint64_t)__double2ull_rn((double)f * 0x1p39); }
 
-template <int P, int U, int FMT, int LK, bool FROM_STATE, bool WIDE, bool ACC32 = false>
-__device__ void fitness_body(const FitLaunch& a, const int blk) {
+// s_ones: LDS for the brick bits (staged here when they fit; `staged` tells
+// whether the previous item of a persistent workgroup left them there), or
+// nullptr.  Every exit before the barrier is uniform over the workgroup.
+template <int P, int U, int FMT, int LK, bool FROM_STATE, bool WIDE, bool ACC32 = false, int WG = 4>
+__device__ void fitness_body(const FitLaunch& a, const int blk, uint32_t* s_ones, bool staged = false) {
     constexpr int kU = U;
     constexpr int kStep = kWave * kU;
     const int lane = threadIdx.x & 63;
@@ -225,10 +316,19 @@ __device__ void fitness_body(const FitLaunch& a, const int blk) {
     const int s8 = a.splits >> 3;
     const int r = blk % a.splits;
     const int split = (r & 7) * s8 + (r >> 3);
-    const int group = (blk / a.splits) * 4 + (threadIdx.x >> 6);
+    const int group = (blk / a.splits) * WG + (threadIdx.x >> 6);
     const int p0 = group * P;
-    if (p0 >= a.n) return;
     if (FROM_STATE && (a.st->stopped || switch_skips(a))) return;
+    // Evaluations outside the grid or in a brick that holds only +1 are
+    // counted (see nout below); kLds: the brick bits are read from LDS
+    constexpr bool kCount = (LK == ROSE_LOOKUP_NEAREST) && !ACC32 && !WIDE;
+    const uint32_t words = ones_words(a.g);
+    const bool lds = kCount && s_ones != nullptr && words <= kOnesLdsWords;
+    if (lds && !staged) {
+        for (uint32_t w = threadIdx.x; w < words; w += kWave * WG) s_ones[w] = a.g.ones[w];
+        __syncthreads();
+    }
+    if (p0 >= a.n) return;
     const int m = a.count_dev ? *a.count_dev : a.count;
 
     // particle transforms: lane l < P builds particle p0 + l
@@ -282,7 +382,6 @@ __device__ void fitness_body(const FitLaunch& a, const int blk) {
     // the search spreads the particles far from the surfaces it spares the
     // gathers that land in free space (a fifth of all evaluations when the
     // axis lengths are 0.2).
-    constexpr bool kCount = (LK == ROSE_LOOKUP_NEAREST) && !ACC32 && !WIDE;
     int nout[P];
 #pragma unroll
     for (int p = 0; p < P; ++p) {
@@ -290,7 +389,7 @@ __device__ void fitness_body(const FitLaunch& a, const int blk) {
         accf[p] = 0.0f;
         nout[p] = 0;
     }
-    auto eval = [&](const float4 (&x)[kU], const bool (&okl)[kU], float (&v)[kU][P]) {
+    auto eval = [&](auto from_lds, const float4 (&x)[kU], const bool (&okl)[kU], float (&v)[kU][P]) {
         float gx[kU * P], gy[kU * P], gz[kU * P], w[kU * P];
         if constexpr (kCount) {
             // one particle's kU addresses at a time (the scheduling barriers
@@ -306,10 +405,22 @@ __device__ void fitness_body(const FitLaunch& a, const int blk) {
                     gx[k] = xf_row(S[p][0], S[p][1], S[p][2], S[p][3], x[u].x, x[u].y, x[u].z);
                     gy[k] = xf_row(S[p][4], S[p][5], S[p][6], S[p][7], x[u].x, x[u].y, x[u].z);
                     gz[k] = xf_row(S[p][8], S[p][9], S[p][10], S[p][11], x[u].x, x[u].y, x[u].z);
-                    bool in = nearest_offset<false>(g, ext, gx[k], gy[k], gz[k], &off[k]);
-                    if (in && brick_all_ones(pb, off[k])) {
-                        in = false;
-                        off[k] = 0xffffffffu;
+                    bool in;
+                    if constexpr (decltype(from_lds)::value) {
+                        const uint32_t o =
+                            brick_offset(g, (uint32_t)gx[k], (uint32_t)gy[k], (uint32_t)gz[k]);
+                        in = (__float_as_uint(gx[k]) < ext.bx) & (__float_as_uint(gy[k]) < ext.by) &
+                             (__float_as_uint(gz[k]) < ext.bz);
+                        // (outside the grid o is any value: clamped to the staged words)
+                        const uint32_t w = s_ones[min(o >> 14, words - 1u)];
+                        in = in & (__builtin_amdgcn_ubfe(w, o >> 9, 1) == 0u);
+                        off[k] = in ? o : 0xffffffffu;
+                    } else {
+                        in = nearest_offset<false>(g, ext, gx[k], gy[k], gz[k], &off[k]);
+                        if (in && brick_all_ones(pb, off[k])) {
+                            in = false;
+                            off[k] = 0xffffffffu;
+                        }
                     }
                     nout[p] += __builtin_popcountll(__builtin_amdgcn_ballot_w64(!in && okl[u]));
                     __builtin_amdgcn_sched_barrier(0);
@@ -341,40 +452,44 @@ __device__ void fitness_body(const FitLaunch& a, const int blk) {
     // empty slice loads nothing (with no points at all the point buffer may
     // not exist) and writes a zero partial sum.
     const int nfull = (j1 > j0) ? (j1 - j0) / kStep : 0;
-    float4 xn[kU];
-    if (j1 > j0) {
-#pragma unroll
-        for (int u = 0; u < kU; ++u) xn[u] = a.pts[min(j0 + u * kWave + lane, j1 - 1)];
-    }
-    for (int st = 0; st < nfull; ++st) {
-        float4 x[kU];
-        const int jn = j0 + (st + 1) * kStep;
-#pragma unroll
-        for (int u = 0; u < kU; ++u) {
-            x[u] = xn[u];
-            xn[u] = a.pts[min(jn + u * kWave + lane, j1 - 1)];
-        }
-        float v[kU][P];
-        eval(x, all, v);
-#pragma unroll
-        for (int u = 0; u < kU; ++u)
-#pragma unroll
-            for (int p = 0; p < P; ++p) add_sq<ACC32>(acc[p], accf[p], v[u][p]);
-    }
-    // the last, partial step: lanes past the slice end add nothing
     const int jt = j0 + nfull * kStep;
-    if (jt < j1) {
-        bool ok[kU];
+    auto steps = [&](auto from_lds) {
+        float4 xn[kU];
+        if (j1 > j0) {
 #pragma unroll
-        for (int u = 0; u < kU; ++u) ok[u] = jt + u * kWave + lane < j1;
-        float v[kU][P];
-        eval(xn, ok, v);
-#pragma unroll
-        for (int u = 0; u < kU; ++u) {
-#pragma unroll
-            for (int p = 0; p < P; ++p) add_sq<ACC32>(acc[p], accf[p], ok[u] ? v[u][p] : 0.0f);
+            for (int u = 0; u < kU; ++u) xn[u] = a.pts[min(j0 + u * kWave + lane, j1 - 1)];
         }
-    }
+        for (int st = 0; st < nfull; ++st) {
+            float4 x[kU];
+            const int jn = j0 + (st + 1) * kStep;
+#pragma unroll
+            for (int u = 0; u < kU; ++u) {
+                x[u] = xn[u];
+                xn[u] = a.pts[min(jn + u * kWave + lane, j1 - 1)];
+            }
+            float v[kU][P];
+            eval(from_lds, x, all, v);
+#pragma unroll
+            for (int u = 0; u < kU; ++u)
+#pragma unroll
+                for (int p = 0; p < P; ++p) add_sq<ACC32>(acc[p], accf[p], v[u][p]);
+        }
+        // the last, partial step: lanes past the slice end add nothing
+        if (jt < j1) {
+            bool ok[kU];
+#pragma unroll
+            for (int u = 0; u < kU; ++u) ok[u] = jt + u * kWave + lane < j1;
+            float v[kU][P];
+            eval(from_lds, xn, ok, v);
+#pragma unroll
+            for (int u = 0; u < kU; ++u) {
+#pragma unroll
+                for (int p = 0; p < P; ++p) add_sq<ACC32>(acc[p], accf[p], ok[u] ? v[u][p] : 0.0f);
+            }
+        }
+    };
+    if (lds) steps(std::bool_constant<kCount>{});
+    else steps(std::false_type{});
     // every lane added kU terms per particle in each step it ran (lanes past
     // the slice end added 0); remove their kGridBase parts, modulo 2^64
     const uint64_t terms = (uint64_t)kWave * kU * (uint64_t)(nfull + (jt < j1 ? 1 : 0));
@@ -508,25 +623,36 @@ __device__ void fitness_body_pl(const FitLaunch& a, const int blk) {
 constexpr int kPlWaves = 8;
 constexpr int kPlWideMinBlocks = 1024;
 
+// Wavefronts per workgroup of a points-across launch (they share the staged
+// brick bits): 8, with which 32 KB of bits leave the CU its full 32
+// wavefronts, for nearest lookups of launches that keep kPaWideMinBlocks
+// workgroups; else 4.  512^3, 10240 particles x 19200 points, 640 workgroups
+// of 8 per slice: 464 / 555 us (two rooms) with 8, 481 / 592 with 4, 463 /
+// 538 with 16; a 64^3 frame of 1024 particles (256 workgroups of 8): 10
+// iterations 307 us with 8, 295 with 4.  Trilinear lookups stage nothing and
+// have the registers of 3 wavefronts per SIMD: 4 is 4 % faster there.
+constexpr int kPaWaves = 8;
+constexpr int kPaWideMinBlocks = 512;
+
 template <int P, int U, int FMT, int LK, bool FROM_STATE, bool WIDE, bool ACC32 = false, int WG = 4>
-__global__ __launch_bounds__(P == kWave ? kWave * WG : 256) void k_fitness(FitLaunch a) {
+__global__ __launch_bounds__(kWave * WG) void k_fitness(FitLaunch a) {
+    extern __shared__ uint32_t s_dyn[];  // points across: the brick bits
     if constexpr (P == kWave) fitness_body_pl<U, FMT, LK, FROM_STATE, WIDE, ACC32, WG>(a, blockIdx.x);
-    else fitness_body<P, U, FMT, LK, FROM_STATE, WIDE, ACC32>(a, blockIdx.x);
+    else
+        fitness_body<P, U, FMT, LK, FROM_STATE, WIDE, ACC32, WG>(a, blockIdx.x, a.ones_lds ? s_dyn : nullptr);
 }
 
-// work items of the persistent batch kernel (its workgroups: 4 particle
-// groups and one slice (points across the lanes), or 4 groups of 64 and one
-// quarter of a slice (one particle per lane)); also the workgroups of a
-// points-across launch
-int fitness_blocks(const FitLaunch& L, int P) {
+// Work items of the persistent batch kernel: 4 or 8 particle groups
+// (batch_waves) and one slice (points across the lanes), or 4 groups of 64
+// and one quarter of a slice (one particle per lane).
+constexpr int batch_waves(int P, int lk) { return P != kWave && lk == ROSE_LOOKUP_NEAREST ? kPaWaves : 4; }
+
+__host__ __device__ inline int blocks_of(const FitLaunch& L, int P, int waves) {
     const int groups = (L.n + P - 1) / P;
-    return (P == kWave ? (groups + 3) / 4 * kPartSub : (groups + 3) / 4) * L.splits;
+    return (groups + waves - 1) / waves * (P == kWave ? kPartSub : 1) * L.splits;
 }
 
-__device__ inline int fitness_blocks_dev(const FitLaunch& L, int P) {
-    const int groups = (L.n + P - 1) / P;
-    return (P == kWave ? (groups + 3) / 4 * kPartSub : (groups + 3) / 4) * L.splits;
-}
+int fitness_blocks(const FitLaunch& L, int P) { return blocks_of(L, P, batch_waves(P, L.lookup)); }
 
 // Persistent fitness over many tracked sequences of one storage format and
 // lookup (a batch launches one kernel per such group, so each kernel holds a
@@ -543,10 +669,12 @@ __device__ inline int fitness_blocks_dev(const FitLaunch& L, int P) {
 // launch on the stream clears them, and every workgroup leaves once its
 // queue passes `end`.
 template <int P, int U, int FMT, int LK>
-__global__ __launch_bounds__(256) void k_fitness_batch(const FitLaunch* __restrict__ seqs,
-                                                       const int* __restrict__ begin, int count, int base, int end,
-                                                       int* __restrict__ ctr) {
+__global__ __launch_bounds__(kWave * batch_waves(P, LK)) void k_fitness_batch(
+    const FitLaunch* __restrict__ seqs, const int* __restrict__ begin, int count, int base, int end,
+    int* __restrict__ ctr, int ones_lds) {
+    extern __shared__ uint32_t s_dyn[];
     __shared__ int s_k;
+    int last = -1;  // the sequence whose brick bits are staged
     const int xcd = (int)(blockIdx.x & 7u);
     for (;;) {
         if (threadIdx.x == 0) s_k = atomicAdd(&ctr[xcd], 1);
@@ -562,24 +690,35 @@ __global__ __launch_bounds__(256) void k_fitness_batch(const FitLaunch* __restri
         }
         const FitLaunch L = seqs[lo];  // wave-uniform: scalar loads of read-only memory
         const int blk = w - begin[lo];
-        if (blk >= fitness_blocks_dev(L, P)) continue;
+        if (blk >= blocks_of(L, P, batch_waves(P, LK))) continue;
         // the particle-per-lane body synchronises its workgroup once; every
         // branch above is uniform over the workgroup (one item per workgroup)
         if constexpr (P == kWave) fitness_body_pl<U, FMT, LK, true, false>(L, blk);
-        else fitness_body<P, U, FMT, LK, true, false>(L, blk);
+        else {
+            fitness_body<P, U, FMT, LK, true, false, false, batch_waves(P, LK)>(L, blk, ones_lds ? s_dyn : nullptr,
+                                                                               lo == last);
+            last = L.st->stopped ? -1 : lo;  // a stopped sequence's item stages nothing
+        }
     }
+}
+
+// LDS bytes for a volume's brick bits in a points-across launch (0: they are
+// read from memory, or not at all)
+int ones_lds_bytes(const Grid& g, int lk, int P) {
+    const uint32_t w = ones_words(g);
+    return P != kWave && lk == ROSE_LOOKUP_NEAREST && w <= kOnesLdsWords ? (int)(4u * w) : 0;
 }
 
 // A persistent grid must fit on the device at once: workgroups that only
 // start when others finish would take their full static share of items late.
 // grid = min(requested, resident workgroups of this kernel), a multiple of 8.
 template <typename K>
-static int resident_grid(K kernel, int requested) {
+static int resident_grid(K kernel, int requested, int threads, int lds) {
     int dev = 0, cus = 0, per_cu = 0;
     if (hipGetDevice(&dev) != hipSuccess ||
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-        hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void*>(kernel), 256, 0) !=
-            hipSuccess ||
+        hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void*>(kernel), threads,
+                                                     (size_t)lds) != hipSuccess ||
         per_cu < 1)
         return std::max(8, requested / 8 * 8);
     return std::max(8, std::min(requested, cus * per_cu) / 8 * 8);
@@ -587,55 +726,58 @@ static int resident_grid(K kernel, int requested) {
 
 template <int P, int U, int FMT, int LK>
 static void launch_batch_kernel(const FitLaunch* seqs, const int* begin, int count, int base, int end, int grid,
-                                int* ctr, hipStream_t s) {
-    hipLaunchKernelGGL((k_fitness_batch<P, U, FMT, LK>), dim3(grid), dim3(256), 0, s, seqs, begin, count, base, end,
-                       ctr);
+                                int lds, int* ctr, hipStream_t s) {
+    hipLaunchKernelGGL((k_fitness_batch<P, U, FMT, LK>), dim3(grid), dim3(kWave * batch_waves(P, LK)),
+                       LK == ROSE_LOOKUP_NEAREST ? (unsigned)lds : 0u, s, seqs, begin, count, base, end, ctr,
+                       LK == ROSE_LOOKUP_NEAREST && lds > 0);
 }
 
 template <int P, int U>
-static int batch_grid_shape(int fmt, int lk, int requested) {
+static int batch_grid_shape(int fmt, int lk, int requested, int lds) {
+    const int threads = kWave * batch_waves(P, lk);
+    if (lk == ROSE_LOOKUP_TRILINEAR) lds = 0;
     if (fmt == ROSE_TSDF_F32)
         return lk == ROSE_LOOKUP_TRILINEAR
-                   ? resident_grid(&k_fitness_batch<P, U, ROSE_TSDF_F32, ROSE_LOOKUP_TRILINEAR>, requested)
-                   : resident_grid(&k_fitness_batch<P, U, ROSE_TSDF_F32, ROSE_LOOKUP_NEAREST>, requested);
+                   ? resident_grid(&k_fitness_batch<P, U, ROSE_TSDF_F32, ROSE_LOOKUP_TRILINEAR>, requested, threads, lds)
+                   : resident_grid(&k_fitness_batch<P, U, ROSE_TSDF_F32, ROSE_LOOKUP_NEAREST>, requested, threads, lds);
     if (fmt == ROSE_TSDF_F16)
         return lk == ROSE_LOOKUP_TRILINEAR
-                   ? resident_grid(&k_fitness_batch<P, U, ROSE_TSDF_F16, ROSE_LOOKUP_TRILINEAR>, requested)
-                   : resident_grid(&k_fitness_batch<P, U, ROSE_TSDF_F16, ROSE_LOOKUP_NEAREST>, requested);
+                   ? resident_grid(&k_fitness_batch<P, U, ROSE_TSDF_F16, ROSE_LOOKUP_TRILINEAR>, requested, threads, lds)
+                   : resident_grid(&k_fitness_batch<P, U, ROSE_TSDF_F16, ROSE_LOOKUP_NEAREST>, requested, threads, lds);
     return lk == ROSE_LOOKUP_TRILINEAR
-               ? resident_grid(&k_fitness_batch<P, U, ROSE_TSDF_SN16, ROSE_LOOKUP_TRILINEAR>, requested)
-               : resident_grid(&k_fitness_batch<P, U, ROSE_TSDF_SN16, ROSE_LOOKUP_NEAREST>, requested);
+               ? resident_grid(&k_fitness_batch<P, U, ROSE_TSDF_SN16, ROSE_LOOKUP_TRILINEAR>, requested, threads, lds)
+               : resident_grid(&k_fitness_batch<P, U, ROSE_TSDF_SN16, ROSE_LOOKUP_NEAREST>, requested, threads, lds);
 }
 
 // grid of the persistent batch launch for a group (host query; call outside
 // stream capture)
-int batch_grid(int P, int U, int fmt, int lk, int requested) {
-    if (P == kWave && U == 8) return batch_grid_shape<kWave, 8>(fmt, lk, requested);
-    if (P == 8 && U == 4) return batch_grid_shape<8, 4>(fmt, lk, requested);
-    if (P == 4 && U == 8) return batch_grid_shape<4, 8>(fmt, lk, requested);
-    if (P == 8 && U == 2) return batch_grid_shape<8, 2>(fmt, lk, requested);
-    if (P == 4 && U == 4) return batch_grid_shape<4, 4>(fmt, lk, requested);
-    return batch_grid_shape<4, 2>(fmt, lk, requested);
+int batch_grid(int P, int U, int fmt, int lk, int requested, int lds) {
+    if (P == kWave && U == 8) return batch_grid_shape<kWave, 8>(fmt, lk, requested, lds);
+    if (P == 8 && U == 4) return batch_grid_shape<8, 4>(fmt, lk, requested, lds);
+    if (P == 4 && U == 8) return batch_grid_shape<4, 8>(fmt, lk, requested, lds);
+    if (P == 8 && U == 2) return batch_grid_shape<8, 2>(fmt, lk, requested, lds);
+    if (P == 4 && U == 4) return batch_grid_shape<4, 4>(fmt, lk, requested, lds);
+    return batch_grid_shape<4, 2>(fmt, lk, requested, lds);
 }
 
 template <int P, int U>
 static void launch_batch_shape(const FitLaunch* seqs, const int* begin, int count, int base, int end, int grid,
-                               int fmt, int lk, int* ctr, hipStream_t s) {
+                               int lds, int fmt, int lk, int* ctr, hipStream_t s) {
     if (fmt == ROSE_TSDF_F32) {
         if (lk == ROSE_LOOKUP_TRILINEAR)
-            launch_batch_kernel<P, U, ROSE_TSDF_F32, ROSE_LOOKUP_TRILINEAR>(seqs, begin, count, base, end, grid, ctr, s);
+            launch_batch_kernel<P, U, ROSE_TSDF_F32, ROSE_LOOKUP_TRILINEAR>(seqs, begin, count, base, end, grid, lds, ctr, s);
         else
-            launch_batch_kernel<P, U, ROSE_TSDF_F32, ROSE_LOOKUP_NEAREST>(seqs, begin, count, base, end, grid, ctr, s);
+            launch_batch_kernel<P, U, ROSE_TSDF_F32, ROSE_LOOKUP_NEAREST>(seqs, begin, count, base, end, grid, lds, ctr, s);
     } else if (fmt == ROSE_TSDF_F16) {
         if (lk == ROSE_LOOKUP_TRILINEAR)
-            launch_batch_kernel<P, U, ROSE_TSDF_F16, ROSE_LOOKUP_TRILINEAR>(seqs, begin, count, base, end, grid, ctr, s);
+            launch_batch_kernel<P, U, ROSE_TSDF_F16, ROSE_LOOKUP_TRILINEAR>(seqs, begin, count, base, end, grid, lds, ctr, s);
         else
-            launch_batch_kernel<P, U, ROSE_TSDF_F16, ROSE_LOOKUP_NEAREST>(seqs, begin, count, base, end, grid, ctr, s);
+            launch_batch_kernel<P, U, ROSE_TSDF_F16, ROSE_LOOKUP_NEAREST>(seqs, begin, count, base, end, grid, lds, ctr, s);
     } else {
         if (lk == ROSE_LOOKUP_TRILINEAR)
-            launch_batch_kernel<P, U, ROSE_TSDF_SN16, ROSE_LOOKUP_TRILINEAR>(seqs, begin, count, base, end, grid, ctr, s);
+            launch_batch_kernel<P, U, ROSE_TSDF_SN16, ROSE_LOOKUP_TRILINEAR>(seqs, begin, count, base, end, grid, lds, ctr, s);
         else
-            launch_batch_kernel<P, U, ROSE_TSDF_SN16, ROSE_LOOKUP_NEAREST>(seqs, begin, count, base, end, grid, ctr, s);
+            launch_batch_kernel<P, U, ROSE_TSDF_SN16, ROSE_LOOKUP_NEAREST>(seqs, begin, count, base, end, grid, lds, ctr, s);
     }
 }
 
@@ -645,14 +787,14 @@ bool batch_shape_valid(int P, int U) {
 }
 
 rose_status launch_fitness_batch(const FitLaunch* seqs_dev, const int* begin_dev, int count, int base, int end,
-                                 int grid, int P, int U, int fmt, int lk, int* ctr_dev, hipStream_t s) {
+                                 int grid, int lds, int P, int U, int fmt, int lk, int* ctr_dev, hipStream_t s) {
     if (P == kWave && U == 8)
-        launch_batch_shape<kWave, 8>(seqs_dev, begin_dev, count, base, end, grid, fmt, lk, ctr_dev, s);
-    else if (P == 8 && U == 4) launch_batch_shape<8, 4>(seqs_dev, begin_dev, count, base, end, grid, fmt, lk, ctr_dev, s);
-    else if (P == 4 && U == 8) launch_batch_shape<4, 8>(seqs_dev, begin_dev, count, base, end, grid, fmt, lk, ctr_dev, s);
-    else if (P == 8 && U == 2) launch_batch_shape<8, 2>(seqs_dev, begin_dev, count, base, end, grid, fmt, lk, ctr_dev, s);
-    else if (P == 4 && U == 4) launch_batch_shape<4, 4>(seqs_dev, begin_dev, count, base, end, grid, fmt, lk, ctr_dev, s);
-    else launch_batch_shape<4, 2>(seqs_dev, begin_dev, count, base, end, grid, fmt, lk, ctr_dev, s);
+        launch_batch_shape<kWave, 8>(seqs_dev, begin_dev, count, base, end, grid, lds, fmt, lk, ctr_dev, s);
+    else if (P == 8 && U == 4) launch_batch_shape<8, 4>(seqs_dev, begin_dev, count, base, end, grid, lds, fmt, lk, ctr_dev, s);
+    else if (P == 4 && U == 8) launch_batch_shape<4, 8>(seqs_dev, begin_dev, count, base, end, grid, lds, fmt, lk, ctr_dev, s);
+    else if (P == 8 && U == 2) launch_batch_shape<8, 2>(seqs_dev, begin_dev, count, base, end, grid, lds, fmt, lk, ctr_dev, s);
+    else if (P == 4 && U == 4) launch_batch_shape<4, 4>(seqs_dev, begin_dev, count, base, end, grid, lds, fmt, lk, ctr_dev, s);
+    else launch_batch_shape<4, 2>(seqs_dev, begin_dev, count, base, end, grid, lds, fmt, lk, ctr_dev, s);
     ROSE_CHECK_HIP(hipGetLastError());
     return ROSE_OK;
 }
@@ -732,32 +874,35 @@ void fit_launch_shape(const rose_tsdf* h, int lk, int* p, int* u, float* thr_vox
 }
 
 template <int P, int U, int FMT, int LK, bool WIDE, int WG>
-static void launch_pu_wg(const FitLaunch& L, unsigned blocks, hipStream_t s) {
-    const dim3 threads(P == kWave ? kWave * WG : 256);
+static void launch_pu_wg(const FitLaunch& Lin, unsigned blocks, hipStream_t s) {
+    const dim3 threads(kWave * WG);
+    FitLaunch L = Lin;
+    const unsigned lds = (WIDE || L.acc32) ? 0u : (unsigned)ones_lds_bytes(L.g, LK, P);
+    L.ones_lds = lds > 0;
     if (L.T32)
-        hipLaunchKernelGGL((k_fitness<P, U, FMT, LK, false, WIDE, false, WG>), dim3(blocks), threads, 0, s, L);
+        hipLaunchKernelGGL((k_fitness<P, U, FMT, LK, false, WIDE, false, WG>), dim3(blocks), threads, lds, s, L);
     else if constexpr (FMT == ROSE_TSDF_F32 && !WIDE) {
         if (L.acc32)
-            hipLaunchKernelGGL((k_fitness<P, U, FMT, LK, true, WIDE, true, WG>), dim3(blocks), threads, 0, s, L);
+            hipLaunchKernelGGL((k_fitness<P, U, FMT, LK, true, WIDE, true, WG>), dim3(blocks), threads, lds, s, L);
         else
-            hipLaunchKernelGGL((k_fitness<P, U, FMT, LK, true, WIDE, false, WG>), dim3(blocks), threads, 0, s, L);
+            hipLaunchKernelGGL((k_fitness<P, U, FMT, LK, true, WIDE, false, WG>), dim3(blocks), threads, lds, s, L);
     } else
-        hipLaunchKernelGGL((k_fitness<P, U, FMT, LK, true, WIDE, false, WG>), dim3(blocks), threads, 0, s, L);
+        hipLaunchKernelGGL((k_fitness<P, U, FMT, LK, true, WIDE, false, WG>), dim3(blocks), threads, lds, s, L);
 }
 
 template <int P, int U, int FMT, int LK, bool WIDE>
 static void launch_pu(const FitLaunch& L, hipStream_t s) {
-    // points across: 4 groups per workgroup and one slice; particle per
+    // points across: WG groups per workgroup and one slice; particle per
     // lane: WG groups of 64 per workgroup and one quarter-slice
-    if constexpr (P == kWave) {
-        const int groups = (L.n + kWave - 1) / kWave;
-        const int wide = (groups + kPlWaves - 1) / kPlWaves * kPartSub * L.splits;
-        if (wide >= kPlWideMinBlocks) {
-            launch_pu_wg<P, U, FMT, LK, WIDE, kPlWaves>(L, (unsigned)wide, s);
+    constexpr int kWide = P == kWave ? kPlWaves : kPaWaves;
+    if constexpr (P == kWave || (LK == ROSE_LOOKUP_NEAREST && !WIDE)) {
+        const int wide = blocks_of(L, P, kWide);
+        if (wide >= (P == kWave ? kPlWideMinBlocks : kPaWideMinBlocks)) {
+            launch_pu_wg<P, U, FMT, LK, WIDE, kWide>(L, (unsigned)wide, s);
             return;
         }
     }
-    launch_pu_wg<P, U, FMT, LK, WIDE, 4>(L, (unsigned)fitness_blocks(L, P), s);
+    launch_pu_wg<P, U, FMT, LK, WIDE, 4>(L, (unsigned)blocks_of(L, P, 4), s);
 }
 
 template <int FMT, int LK>

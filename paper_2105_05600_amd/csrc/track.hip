@@ -615,6 +615,7 @@ struct BatchGroup {
     int first, count;  // positions in the group-ordered work arrays
     int base, end;     // work items [base, end)
     int grid;
+    int lds;           // bytes for the largest staged brick bits of its volumes
 };
 
 // Sequences in the switching mode whose iteration holds at least this many
@@ -736,7 +737,7 @@ static rose_status batch_enqueue(rose_batch* b, hipStream_t s) {
         for (size_t q = 0; q < b->groups.size(); ++q) {
             const BatchGroup& gr = b->groups[q];
             rose_status st = launch_fitness_batch(b->fit_dev + gr.first, b->begin_dev + gr.first, gr.count, gr.base,
-                                                  gr.end, gr.grid, b->P, b->U, gr.fmt, gr.lk, b->ctr_dev + 8 * q, s);
+                                                  gr.end, gr.grid, gr.lds, b->P, b->U, gr.fmt, gr.lk, b->ctr_dev + 8 * q, s);
             if (st != ROSE_OK) return st;
         }
         for (const FitLaunch& L : b->own_fl) {
@@ -929,7 +930,9 @@ rose_status pso_batch_create(int32_t count, rose_tsdf* const* tsdfs, const rose_
         gr.count = e - k;
         gr.base = begin[k];
         gr.end = begin[e];
-        gr.grid = batch_grid(P, U, gr.fmt, gr.lk, gr.end - gr.base);
+        gr.lds = 0;
+        for (int q = k; q < e; ++q) gr.lds = std::max(gr.lds, ones_lds_bytes(tsdfs[order[q]]->g, gr.lk, P));
+        gr.grid = batch_grid(P, U, gr.fmt, gr.lk, gr.end - gr.base, gr.lds);
         b->groups.push_back(gr);
         k = e;
     }
