@@ -289,7 +289,7 @@ static rose_status swarm_track(rose_tsdf* h, const float* depth_dev, const rose_
     if ((g = grow(&h->pts_o, &h->cap_points_o, mmax)) != ROSE_OK) return g;
     if ((g = grow(&h->partial, &h->cap_partial, (int64_t)n * splits * kPartSub)) != ROSE_OK) return g;
     if ((g = grow(&h->F, &h->cap_particles, (int64_t)n)) != ROSE_OK) return g;
-    if (!h->st) ROSE_CHECK_HIP(hipMalloc(&h->st, sizeof(DevState)));
+    if ((g = track_memory(h)) != ROSE_OK) return g;
     if (!h->st_host) ROSE_CHECK_HIP(hipHostMalloc(&h->st_host, sizeof(DevState), hipHostMallocDefault));
     if (h->cap_swarm < n || !h->sw_x) {
         int64_t cap = 0;
@@ -310,6 +310,8 @@ static rose_status swarm_track(rose_tsdf* h, const float* depth_dev, const rose_
     // unprojection, chart state (c_0, r = 1) and the overlap set of c_0
     InitStatic ia;
     ia.st = h->st;
+    ia.work = work_of(h->st);
+    ia.blocks = compact_blocks(mmax, p->flags);
     ia.cam = to_cam(cam);
     ia.levels = 1;
     ia.flags = p->flags;

@@ -1,7 +1,7 @@
 // Per-frame PST pose search (Alg. 1 with the implementation choices of
-// Sec. 4), run entirely on the device: one small setup kernel, then per
-// iteration the fitness kernel (fitness.hip) and a single-workgroup update
-// kernel that folds the fitness into the APS sums, applies CompBestState /
+// Sec. 4), run entirely on the device: one setup kernel, then per iteration
+// the fitness kernel (fitness.hip), a kernel that turns the fitness sums into
+// APS terms, and a step kernel that adds these, applies CompBestState /
 // CompAxisLength / MovePST and the corner cases, and compacts the overlap
 // set for the next iteration.  The host enqueues the whole loop and
 // synchronises once.
@@ -11,57 +11,50 @@
 
 namespace rose {
 
-// Stride-s unprojection of a frame into pts (8x8-sample tile order,
-// order-preserving compaction); returns the number of valid samples.
-__device__ int unproject_level(const Cam& cam, const float* depth, int stride, float4* pts, int* lds) {
-    const int su = (cam.W + stride - 1) / stride;
-    const int sv = (cam.H + stride - 1) / stride;
-    const int total = sample_count(su, sv, true);
-    int m = 0;
-    for (int q0 = 0; q0 < total; q0 += blockDim.x) {
-        const int q = q0 + threadIdx.x;
-        int keep = 0;
-        float4 x = make_float4(0, 0, 0, 0);
-        int uu, vv;
-        if (q < total && sample_at(q, su, sv, true, &uu, &vv)) {
-            const int u = uu * stride, v = vv * stride;
-            const float z = depth[(int64_t)v * cam.W + u];
-            if (z > 0.0f) {
-                keep = 1;
-                x = unproject_px(cam, u, v, z);
-            }
-        }
-        int tot;
-        const int pos = block_scan_flag(keep, lds, &tot);
-        if (keep) pts[m + pos] = x;
-        m += tot;
+// positions of the workgroup's flagged threads in an output list that other
+// workgroups append to as well: in thread order within the workgroup, after
+// the `count` entries that were reserved before (one atomic per workgroup).
+// 1024 threads; lds: 18 ints.  Two barriers.
+__device__ inline int append_positions(bool flag, uint32_t* count, int* lds) {
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+    const uint64_t m = __ballot(flag);
+    if (lane == 0) lds[wid] = __popcll(m);
+    __syncthreads();
+    int offs = 0, acc = 0;
+#pragma unroll
+    for (int w = 0; w < 16; ++w) {
+        const int c = lds[w];
+        offs += w < wid ? c : 0;
+        acc += c;
     }
-    return m;
+    if (threadIdx.x == 0) lds[17] = acc ? (int)atomicAdd(count, (uint32_t)acc) : 0;
+    __syncthreads();
+    return lds[17] + offs + __popcll(m & ((1ull << lane) - 1ull));
 }
 
 // Unprojection of the frame at every resolution level, device-state
-// initialisation and the first overlap set (level 0).
-__device__ void track_init_body(const InitStatic& a, const FrameIn& in) {
-    __shared__ int lds[17];
+// initialisation and the first overlap set (level 0).  Each of a.blocks
+// workgroups takes a contiguous part of every level's samples (8x8-sample
+// tile order) and appends its points; the last one to finish sets the counts.
+// One 640x480 frame at stride 4: 49 us with one workgroup, 8 us with 19.
+__device__ void track_init_body(const InitStatic& a, const FrameIn& in, int block) {
+    __shared__ int lds[18], lds_o[18];
     __shared__ float A[12];
     if (!in.active) {
-        if (threadIdx.x == 0) {
+        if (threadIdx.x == 0 && block == 0) {
             a.st->stopped = 1;
             a.st->k = 0;
             a.st->n_points = -1;
         }
         return;
     }
-    __shared__ int lvl_m[ROSE_MAX_LEVELS];
-    if (threadIdx.x < ROSE_MAX_LEVELS) lvl_m[threadIdx.x] = 0;
-    int m = 0, m_any = 0;
-    for (int l = 0; l < a.levels; ++l) {
-        const int ml = unproject_level(a.cam, in.depth, a.stride[l], a.pts + a.offset[l], lds);
-        if (threadIdx.x == 0) lvl_m[l] = ml;  // read back by thread 0 only
-        if (l == 0) m = ml;
-        m_any += ml;
-    }
     if (threadIdx.x == 0) {
+        double Tc[12], Ad[12];
+        pose_matrix(in.qc, in.tc, Tc);
+        relative_transform(in.Tprev, Tc, Ad);
+        for (int i = 0; i < 12; ++i) A[i] = (float)Ad[i];
+    }
+    if (threadIdx.x == 64 && block == 0) {
         DevState* s = a.st;
         for (int i = 0; i < 4; ++i) s->qc[i] = in.qc[i];
         for (int i = 0; i < 3; ++i) s->tc[i] = in.tc[i];
@@ -71,27 +64,60 @@ __device__ void track_init_body(const InitStatic& a, const FrameIn& in) {
         s->rho_last = 0.5;
         s->thr = 0.0;
         s->k = 0;
-        s->stopped = (m_any == 0) ? 1 : 0;
         s->empty_streak = 0;
         s->have_rho = 0;
-        s->n_points = m;
-        for (int l = 0; l < ROSE_MAX_LEVELS; ++l) s->lvl_points[l] = lvl_m[l];
-        s->n_overlap = 0;
         s->status = 0;
-        double Tc[12], Ad[12];
-        pose_matrix(in.qc, in.tc, Tc);
-        relative_transform(in.Tprev, Tc, Ad);
-        for (int i = 0; i < 12; ++i) A[i] = (float)Ad[i];
     }
     __syncthreads();
-    const int nO = overlap_compact(a.cam, A, (a.flags & ROSE_FLAG_NO_OVERLAP) != 0, a.pts, m, a.pts_o, lds);
-    if (threadIdx.x == 0) a.st->n_overlap = nO;
+    const bool all = (a.flags & ROSE_FLAG_NO_OVERLAP) != 0;
+    for (int l = 0; l < a.levels; ++l) {
+        const int stride = a.stride[l];
+        const int su = (a.cam.W + stride - 1) / stride, sv = (a.cam.H + stride - 1) / stride;
+        const int total = sample_count(su, sv, true), bd = (int)blockDim.x;
+        const int per = (total + a.blocks * bd - 1) / (a.blocks * bd) * bd;  // samples per workgroup
+        const int q1 = min(total, (block + 1) * per);
+        for (int q0 = block * per; q0 < q1; q0 += bd) {
+            const int q = q0 + (int)threadIdx.x;
+            bool keep = false;
+            float4 x = make_float4(0, 0, 0, 0);
+            int uu, vv;
+            if (q < q1 && sample_at(q, su, sv, true, &uu, &vv)) {
+                const int u = uu * stride, v = vv * stride;
+                const float z = in.depth[(int64_t)v * a.cam.W + u];
+                if (z > 0.0f) {
+                    keep = true;
+                    x = unproject_px(a.cam, u, v, z);
+                }
+            }
+            const int pos = append_positions(keep, &a.work->pts_count[l], lds);
+            if (keep) a.pts[a.offset[l] + pos] = x;
+            if (l == 0) {
+                const bool over = keep && (all || overlap_keep(a.cam, A, x));
+                const int po = append_positions(over, &a.work->overlap_count, lds_o);
+                if (over) a.pts_o[po] = x;
+            }
+        }
+    }
+    if (threadIdx.x == 0 && atomicAdd(&a.work->ticket, 1u) == (uint32_t)a.blocks - 1u) {
+        // every workgroup's counts are in (each had its atomics' results
+        // before it took its ticket)
+        uint32_t any = 0;
+        for (int l = 0; l < ROSE_MAX_LEVELS; ++l) {
+            const uint32_t ml = atomicExch(&a.work->pts_count[l], 0u);
+            a.st->lvl_points[l] = (int)ml;
+            if (l == 0) a.st->n_points = (int)ml;
+            any += ml;
+        }
+        a.st->n_overlap = (int)atomicExch(&a.work->overlap_count, 0u);
+        a.st->stopped = any == 0 ? 1 : 0;
+        atomicExch(&a.work->ticket, 0u);
+    }
 }
 
-__global__ __launch_bounds__(1024) void k_track_init(InitStatic a, FrameIn in) { track_init_body(a, in); }
+__global__ __launch_bounds__(1024) void k_track_init(InitStatic a, FrameIn in) { track_init_body(a, in, blockIdx.x); }
 
 rose_status launch_track_init(const InitStatic& a, const FrameIn& in, hipStream_t s) {
-    hipLaunchKernelGGL(k_track_init, dim3(1), dim3(1024), 0, s, a, in);
+    hipLaunchKernelGGL(k_track_init, dim3(a.blocks), dim3(1024), 0, s, a, in);
     ROSE_CHECK_HIP(hipGetLastError());
     return ROSE_OK;
 }
@@ -99,25 +125,26 @@ rose_status launch_track_init(const InitStatic& a, const FrameIn& in, hipStream_
 // the batched fitness launches' per-XCD work counters (n_ctr <= 1024) are
 // cleared by the kernel that precedes each launch on the stream
 __device__ inline void clear_counters(int* ctr, int n_ctr) {
-    if (blockIdx.x == 0 && (int)threadIdx.x < n_ctr) ctr[threadIdx.x] = 0;
+    if (blockIdx.x == 0 && blockIdx.y == 0 && (int)threadIdx.x < n_ctr) ctr[threadIdx.x] = 0;
 }
 
-// one workgroup per sequence; the per-frame inputs are read from pinned host
-// memory (so that a captured graph replays with new inputs)
+// one column of workgroups per sequence; the per-frame inputs are read from
+// pinned host memory (so that a captured graph replays with new inputs)
 __global__ __launch_bounds__(1024) void k_track_init_batch(const InitStatic* a, const FrameIn* in_host, int* ctr,
                                                            int n_ctr) {
     clear_counters(ctr, n_ctr);
+    if ((int)blockIdx.x >= a[blockIdx.y].blocks) return;
     __shared__ FrameIn fin;
     constexpr int kWords = sizeof(FrameIn) / sizeof(uint64_t);
     if (threadIdx.x < kWords)
-        ((uint64_t*)&fin)[threadIdx.x] = ((const volatile uint64_t*)&in_host[blockIdx.x])[threadIdx.x];
+        ((uint64_t*)&fin)[threadIdx.x] = ((const volatile uint64_t*)&in_host[blockIdx.y])[threadIdx.x];
     __syncthreads();
-    track_init_body(a[blockIdx.x], fin);
+    track_init_body(a[blockIdx.y], fin, blockIdx.x);
 }
 
-// F_i of every particle from its slice partials (fixed slice order), before
-// the update: many workgroups, so the update kernel's single workgroup reads
-// n floats instead of n x splits doubles.
+// F_i of every particle from its slice partials, for the comparison
+// optimisers: many workgroups, so their update's single workgroup reads n
+// floats instead of n x splits doubles.
 // one wavefront per particle i (wave-uniform exits)
 __device__ inline void reduce_fitness_body(const UpdateArgs& a, int i) {
     if (i >= a.n || a.st->stopped) return;
@@ -138,131 +165,281 @@ rose_status launch_fitness_reduce(const UpdateArgs& a, hipStream_t s) {
     return ROSE_OK;
 }
 
-// one column of workgroups per sequence
-__global__ __launch_bounds__(256) void k_fitness_reduce_batch(const UpdateArgs* a) {
-    reduce_fitness_body(a[blockIdx.y], blockIdx.x * kReducePerBlock + (int)(threadIdx.x >> 6));
+// The update of an iteration, in two launches.
+//
+// First (track_weights_body): a workgroup per 64 particles reduces their
+// slice sums to fitness values (a wavefront per particle) and these to
+// likelihoods and APS weights; workgroup 0 also copies the state for the
+// second launch, whose workgroups must not read what one of them writes.
+constexpr int kWeightThreads = 512;
+
+// F of particle i (clamped to the last) on the 8 lanes of its group: 8
+// particles per wavefront, each lane adding 2 of every 16 of its particle's
+// slots (16-byte loads, all in flight), then the 8 lanes' integers.
+__device__ inline float fitness_of_8(const UpdateArgs& a, int i, int nO) {
+    const int S = a.splits * kPartSub, t = threadIdx.x & 7;  // S: a multiple of 32, at most 256
+    const ulonglong2* row = (const ulonglong2*)(a.partial + (int64_t)min(i, a.n - 1) * S) + t;
+    uint64_t q = 0;
+    for (int k = 0; k < S / 16; k += 2) {
+        const ulonglong2 u = row[8 * k], v = row[8 * k + 8];
+        q += u.x + u.y + v.x + v.y;
+    }
+#pragma unroll
+    for (int off = 4; off > 0; off >>= 1) q += (uint64_t)__shfl_xor((unsigned long long)q, off, kWave);
+    return fitness_of_sum(a, q, nO);
+}
+constexpr int kSnapWords = offsetof(DevState, aps) / 4;
+
+__device__ void track_weights_body(const UpdateArgs& a, int g) {
+    __shared__ float s_F[kWave];
+    __shared__ float s_F0;  // of particle 0, outside workgroup 0
+    const DevState* st = a.st;
+    if (g == 0)
+        for (int i = threadIdx.x; i < kSnapWords; i += kWeightThreads)
+            ((uint32_t*)&a.work->snap)[i] = ((const uint32_t*)st)[i];
+    if (st->stopped || g * kWave >= a.n) return;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int nO = st->n_overlap, i0 = g * kWave;
+    // the APS threshold rho(s*_{k-1}): the carried Eq. wafit value from k = 2
+    // on; the centre's exact fitness (particle 0) at k = 1 or with
+    // ROSE_FLAG_CENTRE_THRESHOLD
+    const bool centre = st->k == 0 || (a.flags & ROSE_FLAG_CENTRE_THRESHOLD);
+    const float f = fitness_of_8(a, i0 + wave * 8 + (lane >> 3), nO);
+    if ((lane & 7) == 0) s_F[wave * 8 + (lane >> 3)] = f;
+    if (wave == 0 && centre && g != 0) {
+        const float f0 = fitness_of_8(a, 0, nO);
+        if (lane == 0) s_F0 = f0;
+    }
+    __syncthreads();
+    if (wave != 0) return;
+    const int i = i0 + lane;
+    const double rho = exp_rho(-(double)s_F[lane] / a.tau);
+    double rho0 = st->thr;
+    if (centre) rho0 = g == 0 ? __shfl(rho, 0, kWave) : exp_rho(-(double)s_F0 / a.tau);
+    if (i < a.n) aps_terms(a)[i] = make_double2(rho > rho0 ? rho - rho0 : 0.0, rho);
 }
 
-__device__ void track_update_body(const UpdateArgs& a) {
-    __shared__ int lds[17];
-    __shared__ double red[16][9];
+__global__ __launch_bounds__(kWeightThreads) void k_track_weights(UpdateArgs a) { track_weights_body(a, blockIdx.x); }
+
+// one column of workgroups per sequence
+__global__ __launch_bounds__(kWeightThreads) void k_track_weights_batch(const UpdateArgs* a) {
+    track_weights_body(a[blockIdx.y], blockIdx.x);
+}
+
+// what a step changes of the state, in registers
+struct StepState {
+    double qc[4], tc[3], r[6], r1[6], rho_last, thr;
+    int32_t k, stopped, empty_streak, have_rho;
+};
+
+// CompBestState / CompAxisLength / MovePST and the corner cases of Sec. 4
+// from the APS sums.
+__device__ inline void pst_update(const UpdateArgs& a, StepState& s, const double tot[9], double centre,
+                                  double* rho_tilde) {
+    const double rho0 = (s.k == 0 || (a.flags & ROSE_FLAG_CENTRE_THRESHOLD)) ? centre : s.thr;
+    const int aps = (int)tot[0];
+    const double inv_sqrt6 = 1.0 / sqrt(6.0);
+    double rhat[6], rt;
+    if (aps > 0) {
+        const double W = tot[1];
+        double us[6], nv = 0.0;
+        for (int d = 0; d < 6; ++d) {
+            us[d] = tot[3 + d] / W;
+            nv += us[d] * us[d];
+        }
+        nv = sqrt(nv);
+        rt = tot[2] / W;
+        // Eq. rsinter; the rescaling ablation keeps one of its two parts
+        const double iso = (a.flags & ROSE_FLAG_ANISO_ONLY) ? 1.0 : (1.0 - rt);
+        const bool aniso = nv > 0.0 && !(a.flags & ROSE_FLAG_ISO_ONLY);
+        for (int d = 0; d < 6; ++d) rhat[d] = iso * (aniso ? fabs(us[d]) / nv : inv_sqrt6) + a.eps;
+        retract(s.qc, s.tc, us);
+        s.rho_last = rt;
+        s.have_rho = 1;
+        s.empty_streak = 0;
+        if (a.early_stop) {
+            bool small = true;
+            for (int d = 0; d < 6; ++d) small = small && (fabs(us[d]) < a.stop_tol);
+            if (small) s.stopped = 1;
+        }
+    } else {
+        rt = rho0;
+        for (int d = 0; d < 6; ++d) rhat[d] = 2.0 * (1.0 - rho0) * inv_sqrt6;
+        if (!s.have_rho) s.rho_last = rho0;
+        s.empty_streak += 1;
+        if (a.early_stop && s.empty_streak >= 2) s.stopped = 1;
+    }
+    for (int d = 0; d < 6; ++d) s.r[d] = a.beta * s.r[d] + (1.0 - a.beta) * rhat[d];
+    s.thr = (aps > 0) ? rt : rho0;
+    if (s.k == 0)
+        for (int d = 0; d < 6; ++d) s.r1[d] = s.r[d];
+    s.k += 1;
+    if (s.k >= a.max_iters) s.stopped = 1;
+    *rho_tilde = rt;
+}
+
+// Second (track_step_body): every workgroup adds the APS terms -- count, w,
+// w rho, w u_d -- in one fixed order (per thread over its particles tid + j
+// 1024 in increasing j, over the wavefront by butterfly, over the wavefronts
+// in turn) and takes the same step from the same copy of the state, which is
+// not worth a launch of its own; then it tests 1024 points against the new
+// centre and appends those of the next overlap set.  Workgroup 0 writes the
+// state, the last one to finish the set's size.  With one workgroup the
+// points keep their order.  512^3 frame of 10240 particles and 19200 points:
+// both launches 18 us per iteration, against 32 us for a reduction launch and
+// one workgroup that did the rest; the 32 frames of a batch: 19 against 36 us.
+__device__ void track_step_body(const UpdateArgs& a, int block) {
+    __shared__ int lds[18];
+    __shared__ double red[16][9], tot[9];
     __shared__ float A[12];
+    __shared__ DevState s;
     __shared__ int go_on;
-    DevState* st = a.st;
-    if (st->stopped) return;
-    const int nO = st->n_overlap;
-    const float F0 = a.F[0];
-    // APS threshold rho(s*_{k-1}): the carried Eq. wafit value from k = 2 on;
-    // the centre's exact fitness (particle 0) at k = 1 or with
-    // ROSE_FLAG_CENTRE_THRESHOLD
-    const double centre = exp_rho(-(double)F0 / a.tau);
-    const double rho0 = (st->k == 0 || (a.flags & ROSE_FLAG_CENTRE_THRESHOLD)) ? centre : st->thr;
-    double r[6];
-    for (int d = 0; d < 6; ++d) r[d] = st->r[d];
-    // per-thread APS sums: count, sum w, sum w rho, sum w u_d, over the
-    // thread's particles i = threadIdx.x + j blockDim.x in increasing j; the
-    // loads of 8 of them are issued before their arithmetic (latency)
-    double cnt = 0.0, sw = 0.0, swr = 0.0, su[6] = {0, 0, 0, 0, 0, 0};
-    constexpr int kAhead = 8;
-    const int bd = (int)blockDim.x;
-    for (int i0 = threadIdx.x; i0 < a.n; i0 += kAhead * bd) {
-        float f[kAhead], pr[kAhead][6];
+    __shared__ int old_k;
+    __shared__ double rt, centre, r_old[6];
+    __shared__ StepState next;
+    const int tid = (int)threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const UpdateWork& w = *a.work;
+    const int j = block * 1024 + tid;
+    // read before the sums and the step, whose latency these loads overlap
+    const uint32_t snap = ((const uint32_t*)&w.snap)[min(tid, kSnapWords - 1)];
+    const float4 x = a.pts[min(j, a.pts_cap - 1)];
+    double v9[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
+    double r6[6];
+#pragma unroll
+    for (int d = 0; d < 6; ++d) r6[d] = w.snap.r[d];
+    constexpr int kAhead = 5;  // loads in flight before their arithmetic
+    const double2* wr = aps_terms(a);
+    for (int i0 = tid; i0 < a.n; i0 += kAhead * 1024) {
+        double2 t[kAhead];
+        float pr[kAhead][6];
 #pragma unroll
         for (int q = 0; q < kAhead; ++q) {
-            const int i = min(i0 + q * bd, a.n - 1);
-            f[q] = a.F[i];
+            const int i = min(i0 + q * 1024, a.n - 1);
+            t[q] = wr[i];
 #pragma unroll
             for (int d = 0; d < 6; ++d) pr[q][d] = a.pst[6 * (int64_t)i + d];
         }
 #pragma unroll
         for (int q = 0; q < kAhead; ++q) {
-            if (i0 + q * bd >= a.n) break;
-            const double rho = exp_rho(-(double)f[q] / a.tau);
-            if (rho > rho0) {
-                const double w = rho - rho0;
-                cnt += 1.0;
-                sw += w;
-                swr += w * rho;
+            if (i0 + q * 1024 < a.n && t[q].x > 0.0) {
+                v9[0] += 1.0;
+                v9[1] += t[q].x;
+                v9[2] += t[q].x * t[q].y;
 #pragma unroll
-                for (int d = 0; d < 6; ++d) su[d] += w * (r[d] * (double)pr[q][d]);
+                for (int d = 0; d < 6; ++d) v9[3 + d] += t[q].x * (r6[d] * (double)pr[q][d]);
             }
         }
     }
-    double v9[9] = {cnt, sw, swr, su[0], su[1], su[2], su[3], su[4], su[5]};
-    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6, nw = blockDim.x >> 6;
 #pragma unroll
-    for (int e = 0; e < 9; ++e) v9[e] = wave_sum(v9[e]);
-    if (lane == 0)
-        for (int e = 0; e < 9; ++e) red[wid][e] = v9[e];
+    for (int e = 0; e < 9; ++e) {
+        const double v = wave_sum(v9[e]);
+        if (lane == 0) red[wave][e] = v;
+    }
+    if (tid < kSnapWords) ((uint32_t*)&s)[tid] = snap;
+    if (tid == 0) centre = wr[0].y;  // the likelihood of particle 0
     __syncthreads();
-    if (threadIdx.x == 0) {
-        double tot[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
-        for (int w = 0; w < nw; ++w)
-            for (int e = 0; e < 9; ++e) tot[e] += red[w][e];
-        const int aps = (int)tot[0];
-        const double inv_sqrt6 = 1.0 / sqrt(6.0);
-        double rhat[6], rt;
-        if (aps > 0) {
-            const double W = tot[1];
-            double us[6], nv = 0.0;
-            for (int d = 0; d < 6; ++d) {
-                us[d] = tot[3 + d] / W;
-                nv += us[d] * us[d];
-            }
-            nv = sqrt(nv);
-            rt = tot[2] / W;
-            // Eq. rsinter; the rescaling ablation keeps one of its two parts
-            const double iso = (a.flags & ROSE_FLAG_ANISO_ONLY) ? 1.0 : (1.0 - rt);
-            const bool aniso = nv > 0.0 && !(a.flags & ROSE_FLAG_ISO_ONLY);
-            for (int d = 0; d < 6; ++d) rhat[d] = iso * (aniso ? fabs(us[d]) / nv : inv_sqrt6) + a.eps;
-            retract(st->qc, st->tc, us);
-            st->rho_last = rt;
-            st->have_rho = 1;
-            st->empty_streak = 0;
-            if (a.early_stop) {
-                bool small = true;
-                for (int d = 0; d < 6; ++d) small = small && (fabs(us[d]) < a.stop_tol);
-                if (small) st->stopped = 1;
-            }
-        } else {
-            rt = rho0;
-            for (int d = 0; d < 6; ++d) rhat[d] = 2.0 * (1.0 - rho0) * inv_sqrt6;
-            if (!st->have_rho) st->rho_last = rho0;
-            st->empty_streak += 1;
-            if (a.early_stop && st->empty_streak >= 2) st->stopped = 1;
+    if (s.stopped) return;  // (the terms are not this iteration's)
+    if (tid < 9) {
+        double v = 0.0;
+        for (int q = 0; q < 16; ++q) v += red[q][tid];
+        tot[tid] = v;
+    }
+    __syncthreads();
+    if (tid == 0) {
+        StepState h;
+        double Tprev[12], t9[9];
+#pragma unroll
+        for (int d = 0; d < 4; ++d) h.qc[d] = s.qc[d];
+#pragma unroll
+        for (int d = 0; d < 3; ++d) h.tc[d] = s.tc[d];
+#pragma unroll
+        for (int d = 0; d < 6; ++d) {
+            h.r[d] = s.r[d];
+            h.r1[d] = s.r1[d];
+            r_old[d] = h.r[d];
         }
-        for (int d = 0; d < 6; ++d) st->r[d] = a.beta * r[d] + (1.0 - a.beta) * rhat[d];
-        st->thr = (aps > 0) ? rt : rho0;
-        const int k = st->k;
-        st->aps[k] = aps;
-        st->n_overlap_iter[k] = nO;
-        st->rho_iter[k] = rt;
-        st->rho_centre[k] = centre;
-        for (int d = 0; d < 6; ++d) st->r_iter[k][d] = r[d];
-        st->k = k + 1;
-        if (k == 0)
-            for (int d = 0; d < 6; ++d) st->r1[d] = st->r[d];
-        if (k + 1 >= a.max_iters) st->stopped = 1;
-        go_on = !st->stopped;
-        if (go_on) {
-            double Tc[12], Ad[12];
-            pose_matrix(st->qc, st->tc, Tc);
-            relative_transform(st->Tprev, Tc, Ad);
-            for (int i = 0; i < 12; ++i) A[i] = (float)Ad[i];
+#pragma unroll
+        for (int d = 0; d < 12; ++d) Tprev[d] = s.Tprev[d];
+#pragma unroll
+        for (int e = 0; e < 9; ++e) t9[e] = tot[e];
+        h.rho_last = s.rho_last;
+        h.thr = s.thr;
+        h.k = old_k = s.k;
+        h.stopped = 0;
+        h.empty_streak = s.empty_streak;
+        h.have_rho = s.have_rho;
+        double rho_tilde;
+        pst_update(a, h, t9, centre, &rho_tilde);
+        go_on = !h.stopped;
+        double Tc[12], Ad[12];
+        pose_matrix(h.qc, h.tc, Tc);
+        relative_transform(Tprev, Tc, Ad);
+#pragma unroll
+        for (int i = 0; i < 12; ++i) A[i] = (float)Ad[i];
+        if (block == 0) {
+            rt = rho_tilde;
+            next = h;
         }
     }
     __syncthreads();
+    if (block == 0) {
+        DevState* st = a.st;
+        if (tid < 4) st->qc[tid] = next.qc[tid];
+        else if (tid < 7) st->tc[tid - 4] = next.tc[tid - 4];
+        else if (tid < 13) st->r[tid - 7] = next.r[tid - 7];
+        else if (tid < 19) st->r1[tid - 13] = next.r1[tid - 13];
+        else if (tid < 25) st->r_iter[old_k][tid - 19] = r_old[tid - 19];
+        else if (tid == 25) {
+            st->rho_last = next.rho_last;
+            st->thr = next.thr;
+            st->k = next.k;
+            st->stopped = next.stopped;
+            st->empty_streak = next.empty_streak;
+            st->have_rho = next.have_rho;
+        } else if (tid == 26) {
+            st->aps[old_k] = (int)tot[0];
+            st->n_overlap_iter[old_k] = s.n_overlap;
+            st->rho_iter[old_k] = rt;
+            st->rho_centre[old_k] = centre;
+        }
+    }
     if (!go_on) return;
-    const int nO2 = overlap_compact(a.cam, A, (a.flags & ROSE_FLAG_NO_OVERLAP) != 0, a.pts,
-                                    st->lvl_points[a.next_level], a.pts_o, lds);
-    if (threadIdx.x == 0) st->n_overlap = nO2;
+    const int m = s.lvl_points[a.next_level];
+    const bool all = (a.flags & ROSE_FLAG_NO_OVERLAP) != 0;
+    if (a.blocks == 1) {
+        const int n = overlap_compact(a.cam, A, all, a.pts, m, a.pts_o, lds);
+        if (tid == 0) a.st->n_overlap = n;
+        return;
+    }
+    const bool keep = j < m && (all || overlap_keep(a.cam, A, x));
+    const uint64_t ball = __ballot(keep);
+    if (lane == 0) lds[wave] = __popcll(ball);
+    __syncthreads();
+    int offs = 0, acc = 0;  // kept points of the wavefronts before this one, of all
+#pragma unroll
+    for (int q = 0; q < 16; ++q) {
+        const int c = lds[q];
+        offs += q < wave ? c : 0;
+        acc += c;
+    }
+    if (tid == 0) {
+        const uint64_t before = atomicAdd((unsigned long long*)&a.work->pack, (1ull << 32) | (uint32_t)acc);
+        lds[17] = (int)(uint32_t)before;
+        if ((before >> 32) == (uint64_t)a.blocks - 1u) {
+            a.st->n_overlap = (int)(uint32_t)before + acc;
+            atomicExch((unsigned long long*)&a.work->pack, 0ull);
+        }
+    }
+    __syncthreads();
+    if (keep) a.pts_o[lds[17] + offs + __popcll(ball & ((1ull << lane) - 1ull))] = x;
 }
 
-__global__ __launch_bounds__(1024) void k_track_update(UpdateArgs a) { track_update_body(a); }
+__global__ __launch_bounds__(1024) void k_track_step(UpdateArgs a) { track_step_body(a, blockIdx.x); }
 
-__global__ __launch_bounds__(1024) void k_track_update_batch(const UpdateArgs* a, int* ctr, int n_ctr) {
+// one column of workgroups per sequence
+__global__ __launch_bounds__(1024) void k_track_step_batch(const UpdateArgs* a, int* ctr, int n_ctr) {
     clear_counters(ctr, n_ctr);
-    track_update_body(a[blockIdx.x]);
+    if ((int)blockIdx.x < a[blockIdx.y].blocks) track_step_body(a[blockIdx.y], blockIdx.x);
 }
 
 // copy every sequence's device state to pinned host memory
@@ -461,11 +638,13 @@ rose_status pso_track_frame(rose_tsdf* h, const float* depth_dev, const float* p
     if ((g = grow(&h->pts, &h->cap_points, lv_off[L])) != ROSE_OK) return g;
     if ((g = grow(&h->pts_o, &h->cap_points_o, mmax_all)) != ROSE_OK) return g;
     if ((g = grow(&h->partial, &h->cap_partial, partial_need)) != ROSE_OK) return g;
-    if ((g = grow(&h->F, &h->cap_particles, (int64_t)n_particles)) != ROSE_OK) return g;
-    if (!h->st) ROSE_CHECK_HIP(hipMalloc(&h->st, sizeof(DevState)));
+    if ((g = grow(&h->F, &h->cap_particles, fitness_floats(n_particles))) != ROSE_OK) return g;
+    if ((g = track_memory(h)) != ROSE_OK) return g;
     if (!h->st_host) ROSE_CHECK_HIP(hipHostMalloc(&h->st_host, sizeof(DevState), hipHostMallocDefault));
 
     ia.st = h->st;
+    ia.work = work_of(h->st);
+    ia.blocks = compact_blocks(mmax_all, p->flags);
     ia.cam = to_cam(cam, prev_depth_dev);
     ia.flags = p->flags;
     ia.pts = h->pts;
@@ -482,8 +661,7 @@ rose_status pso_track_frame(rose_tsdf* h, const float* depth_dev, const float* p
     const int32_t* lv_order[ROSE_MAX_LEVELS] = {nullptr, nullptr, nullptr, nullptr};
     for (int l = 0; l < L; ++l)
         if ((g = particle_order(h, pst_dev, lv_n[l], s, &lv_order[l])) != ROSE_OK) return g;
-    hipLaunchKernelGGL(k_track_init, dim3(1), dim3(1024), 0, s, ia, fin);
-    ROSE_CHECK_HIP(hipGetLastError());
+    if ((g = launch_track_init(ia, fin, s)) != ROSE_OK) return g;
 
     FitLaunch fl{};
     fl.g = h->g;
@@ -502,6 +680,7 @@ rose_status pso_track_frame(rose_tsdf* h, const float* depth_dev, const float* p
 
     UpdateArgs ua{};
     ua.st = h->st;
+    ua.work = ia.work;
     ua.cam = ia.cam;
     ua.pst = pst_dev;
     ua.partial = h->partial;
@@ -525,13 +704,14 @@ rose_status pso_track_frame(rose_tsdf* h, const float* depth_dev, const float* p
         ua.splits = lv_splits[l];
         ua.pts = h->pts + lv_off[ln];
         ua.next_level = ln;
+        ua.pts_cap = (int32_t)(lv_off[ln + 1] - lv_off[ln]);
+        ua.blocks = compact_blocks(ua.pts_cap, p->flags);
         tok_fit[k] = prof_begin(PROF_FITNESS, s);
         if ((g = launch_fitness(fl, s)) != ROSE_OK) return g;
         prof_end(tok_fit[k], s, 0.0);
         const int tu = prof_begin(PROF_UPDATE, s);
-        hipLaunchKernelGGL(k_fitness_reduce, dim3((ua.n + kReducePerBlock - 1) / kReducePerBlock), dim3(256), 0, s,
-                           ua);
-        hipLaunchKernelGGL(k_track_update, dim3(1), dim3(1024), 0, s, ua);
+        hipLaunchKernelGGL(k_track_weights, dim3((ua.n + kWave - 1) / kWave), dim3(kWeightThreads), 0, s, ua);
+        hipLaunchKernelGGL(k_track_step, dim3(ua.blocks), dim3(1024), 0, s, ua);
         prof_end(tu, s, 0.0);
         ROSE_CHECK_HIP(hipGetLastError());
     }
@@ -624,7 +804,7 @@ struct BatchGroup {
 static int64_t g_batch_own_min = int64_t(1) << 23;
 
 struct rose_batch {
-    int32_t count = 0, K = 0, P = 4, U = 2, total = 0, max_n = 1;
+    int32_t count = 0, K = 0, P = 4, U = 2, total = 0, max_n = 1, max_blocks = 1;
     std::vector<BatchGroup> groups;
     // sequences with launches of their own (the single path's fitness
     // launches, switching included), and those launch records
@@ -690,10 +870,12 @@ static rose_status batch_refresh(rose_batch* b, bool force) {
         L.partial = h->partial;
         InitStatic& ia = b->init_host[i];
         ia.st = h->st;
+        ia.work = work_of(h->st);
         ia.pts = h->pts;
         ia.pts_o = h->pts_o;
         UpdateArgs& ua = b->upd_host[i];
         ua.st = h->st;
+        ua.work = work_of(h->st);
         ua.partial = h->partial;
         ua.F = h->F;
         ua.pts = h->pts;
@@ -730,8 +912,8 @@ static rose_status batch_enqueue(rose_batch* b, hipStream_t s) {
     // (by the init kernel, then by each update kernel); each group has its own
     // 8 counters, so the launches of one round do not disturb each other
     const int n_ctr = 8 * (int)b->groups.size();
-    hipLaunchKernelGGL(k_track_init_batch, dim3(b->count), dim3(1024), 0, s, b->init_dev, b->in_host, b->ctr_dev,
-                       n_ctr);
+    hipLaunchKernelGGL(k_track_init_batch, dim3(b->max_blocks, b->count), dim3(1024), 0, s, b->init_dev, b->in_host,
+                       b->ctr_dev, n_ctr);
     ROSE_CHECK_HIP(hipGetLastError());
     for (int k = 0; k < b->K; ++k) {
         for (size_t q = 0; q < b->groups.size(); ++q) {
@@ -744,10 +926,10 @@ static rose_status batch_enqueue(rose_batch* b, hipStream_t s) {
             rose_status st = launch_fitness(L, s);
             if (st != ROSE_OK) return st;
         }
-        hipLaunchKernelGGL(k_fitness_reduce_batch, dim3((b->max_n + kReducePerBlock - 1) / kReducePerBlock, b->count),
-                           dim3(256), 0, s,
+        hipLaunchKernelGGL(k_track_weights_batch, dim3((b->max_n + kWave - 1) / kWave, b->count), dim3(kWeightThreads), 0, s,
                            b->upd_dev);
-        hipLaunchKernelGGL(k_track_update_batch, dim3(b->count), dim3(1024), 0, s, b->upd_dev, b->ctr_dev, n_ctr);
+        hipLaunchKernelGGL(k_track_step_batch, dim3(b->max_blocks, b->count), dim3(1024), 0, s, b->upd_dev, b->ctr_dev,
+                           n_ctr);
         ROSE_CHECK_HIP(hipGetLastError());
     }
     hipLaunchKernelGGL(k_track_finish_batch, dim3(b->count), dim3(64), 0, s, b->stp_dev, b->out_host);
@@ -848,12 +1030,8 @@ rose_status pso_batch_create(int32_t count, rose_tsdf* const* tsdfs, const rose_
         if ((g = grow(&h->pts, &h->cap_points, mmax)) != ROSE_OK) break;
         if ((g = grow(&h->pts_o, &h->cap_points_o, mmax)) != ROSE_OK) break;
         if ((g = grow(&h->partial, &h->cap_partial, (int64_t)n_particles[i] * splits * kPartSub)) != ROSE_OK) break;
-        if ((g = grow(&h->F, &h->cap_particles, (int64_t)n_particles[i])) != ROSE_OK) break;
-        if (!h->st && hipMalloc(&h->st, sizeof(DevState)) != hipSuccess) {
-            set_error("pso_batch_create: hipMalloc failed");
-            g = ROSE_E_DEVICE;
-            break;
-        }
+        if ((g = grow(&h->F, &h->cap_particles, fitness_floats(n_particles[i]))) != ROSE_OK) break;
+        if ((g = track_memory(h)) != ROSE_OK) break;
         FitLaunch& L = fit[pos[i]];
         L = FitLaunch{};
         L.g = h->g;
@@ -880,6 +1058,8 @@ rose_status pso_batch_create(int32_t count, rose_tsdf* const* tsdfs, const rose_
         InitStatic& ia = init[i];
         ia = InitStatic{};
         ia.st = h->st;
+        ia.work = work_of(h->st);
+        ia.blocks = compact_blocks(mmax, p.flags);
         ia.cam = to_cam(&cams[i]);
         ia.levels = 1;
         ia.flags = p.flags;
@@ -888,6 +1068,10 @@ rose_status pso_batch_create(int32_t count, rose_tsdf* const* tsdfs, const rose_
         ia.pts_o = h->pts_o;
         UpdateArgs& ua = upd[i];
         ua.st = h->st;
+        ua.work = ia.work;
+        ua.blocks = ia.blocks;
+        ua.pts_cap = (int32_t)mmax;
+        b->max_blocks = std::max(b->max_blocks, ua.blocks);
         ua.cam = to_cam(&cams[i]);
         ua.pst = pst_devs[i];
         ua.partial = h->partial;
@@ -1243,7 +1427,7 @@ rose_status pso_batch_track_learned(rose_batch* b, const float* const* depth_dev
         if ((g = grow(&h->pts, &h->cap_points, mmax)) != ROSE_OK) return g;
         if ((g = grow(&h->pts_o, &h->cap_points_o, mmax)) != ROSE_OK) return g;
         if ((g = grow(&h->partial, &h->cap_partial, (int64_t)n_plain[i] * splits * kPartSub)) != ROSE_OK) return g;
-        if ((g = grow(&h->F, &h->cap_particles, (int64_t)n_plain[i])) != ROSE_OK) return g;
+        if ((g = grow(&h->F, &h->cap_particles, fitness_floats(n_plain[i]))) != ROSE_OK) return g;
     }
     const int64_t npx = (int64_t)lp->low_w * lp->low_h, fd = lp->feature_dim;
     float* renders = work_dev;

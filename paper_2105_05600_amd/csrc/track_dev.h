@@ -3,6 +3,8 @@
 // their translation units.
 #pragma once
 
+#include <algorithm>
+
 #include "common.h"
 
 namespace rose {
@@ -119,8 +121,48 @@ __device__ inline int overlap_compact(const Cam& c, const float* A, bool all, co
     return base;
 }
 
+// Scratch of the per-iteration update, behind each handle's DevState in one
+// allocation (track_memory).  The counters are 0 whenever no frame is being
+// tracked: the last workgroup that uses them resets them.
+struct UpdateWork {
+    uint64_t pack;                          // compaction: workgroups done << 32 | points kept so far
+    uint32_t pts_count[ROSE_MAX_LEVELS];    // init: valid samples so far, per level
+    uint32_t overlap_count, ticket;         // init: overlap points so far, workgroups done
+    DevState snap;                          // the state before the update (fields up to lvl_points)
+};
+
+inline UpdateWork* work_of(DevState* st) { return (UpdateWork*)((char*)st + (sizeof(DevState) + 255) / 256 * 256); }
+
+// a handle's device state and update scratch, allocated on first use
+inline rose_status track_memory(rose_tsdf* h) {
+    if (h->st) return ROSE_OK;
+    const size_t bytes = (sizeof(DevState) + 255) / 256 * 256 + sizeof(UpdateWork);
+    void* p = nullptr;
+    ROSE_CHECK_HIP(hipMalloc(&p, bytes));
+    if (hipMemset(p, 0, bytes) != hipSuccess || hipDeviceSynchronize() != hipSuccess) {
+        (void)hipFree(p);
+        set_error("track state: clearing %zu bytes failed", bytes);
+        return ROSE_E_DEVICE;
+    }
+    h->st = (DevState*)p;
+    return ROSE_OK;
+}
+
+// Floats of a handle's F buffer for n particles: their fitness values (the
+// comparison optimisers), then an APS weight and likelihood each.
+inline int64_t fitness_floats(int64_t n) { return (n + 3) / 4 * 4 + 4 * n; }
+
+// Workgroups of 1024 points for the compaction of up to `points` points: one
+// where the order of the points has to be kept (the no-Kahan ablation, whose
+// binary32 sums depend on it; the sums on the grid do not).
+inline int compact_blocks(int64_t points, int flags) {
+    return (flags & ROSE_FLAG_NO_KAHAN) ? 1 : (int)std::max<int64_t>((points + 1023) / 1024, 1);
+}
+
 struct InitStatic {
     DevState* st;
+    UpdateWork* work;
+    int32_t blocks;                        // workgroups of the init launch
     Cam cam;
     int32_t levels;                        // 1, or the multi-resolution level count
     int32_t flags;
@@ -132,6 +174,9 @@ struct InitStatic {
 
 struct UpdateArgs {
     DevState* st;
+    UpdateWork* work;
+    int32_t blocks;     // workgroups of the step launch (compaction of the next overlap set)
+    int32_t pts_cap;    // points that `pts` has room for
     Cam cam;
     const float* pst;
     const uint64_t* partial;
@@ -147,6 +192,18 @@ struct UpdateArgs {
     double beta, eps, tau, stop_tol;
 };
 
+// (w, rho) of every particle; w = rho - threshold for members of the APS, else 0
+__device__ inline double2* aps_terms(const UpdateArgs& a) { return (double2*)(a.F + (a.n + 3) / 4 * 4); }
+
+// F = S / |O| of a grid sum
+__device__ inline float fitness_of_sum(const UpdateArgs& a, uint64_t q, int nO) {
+    const double s = (double)q * kGridScale;
+    double f;
+    if (a.flags & ROSE_FLAG_NO_NORMALIZE) f = s;
+    else f = (nO > 0) ? s / (double)nO : 1.0;
+    return (float)f;
+}
+
 // F_i = S_i / |O| (Eq. normallh) from the slice sums on the 2^-39 grid
 // (exact integer sum, then one rounding to binary64, an exact scaling, one
 // correctly rounded division and one rounding to binary32).  One wavefront
@@ -159,12 +216,7 @@ __device__ inline float final_fitness(const UpdateArgs& a, int i, int nO) {
     const uint64_t* row = a.partial + (int64_t)i * S;
     uint64_t q = 0;
     for (int k = lane; k < S; k += kWave) q += row[k];
-    q = wave_sum_u64(q);
-    const double s = (double)q * kGridScale;
-    double f;
-    if (a.flags & ROSE_FLAG_NO_NORMALIZE) f = s;
-    else f = (nO > 0) ? s / (double)nO : 1.0;
-    return (float)f;
+    return fitness_of_sum(a, wave_sum_u64(q), nO);
 }
 
 rose_status launch_track_init(const InitStatic& a, const FrameIn& in, hipStream_t s);
