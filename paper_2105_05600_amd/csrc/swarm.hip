@@ -311,7 +311,6 @@ static rose_status swarm_track(rose_tsdf* h, const float* depth_dev, const rose_
     InitStatic ia;
     ia.st = h->st;
     ia.work = work_of(h->st);
-    ia.blocks = compact_blocks(mmax, p->flags);
     ia.cam = to_cam(cam);
     ia.levels = 1;
     ia.flags = p->flags;
@@ -321,6 +320,7 @@ static rose_status swarm_track(rose_tsdf* h, const float* depth_dev, const rose_
     }
     ia.pts = h->pts;
     ia.pts_o = h->pts_o;
+    ia.blocks = init_blocks(ia);
     FrameIn fin;
     for (int i = 0; i < 4; ++i) fin.qc[i] = state->pose.q[i];
     for (int i = 0; i < 3; ++i) fin.tc[i] = state->pose.t[i];

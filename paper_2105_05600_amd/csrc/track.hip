@@ -11,50 +11,108 @@
 
 namespace rose {
 
-// positions of the workgroup's flagged threads in an output list that other
-// workgroups append to as well: in thread order within the workgroup, after
-// the `count` entries that were reserved before (one atomic per workgroup).
-// 1024 threads; lds: 18 ints.  Two barriers.
-__device__ inline int append_positions(bool flag, uint32_t* count, int* lds) {
-    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-    const uint64_t m = __ballot(flag);
-    if (lane == 0) lds[wid] = __popcll(m);
-    __syncthreads();
+// Index-ordered output of several workgroups.  A workgroup takes the next
+// ticket, which is its part of the samples or points, so that a part's
+// predecessors are all held by workgroups that run already: it publishes its
+// counts and then waits for theirs, and every such wait ends.  The order is
+// what makes the slices of the fitness kernels compact (appending the parts
+// as they come cost the 512^3 sequence 36 % more HBM reads and 8 % of the
+// fitness time).  The counts travel in one word with the launch they are of,
+// so nothing has to be cleared.
+struct Ordered {
+    uint64_t tag;  // this launch
+    int part;
+};
+
+// one thread; a workgroup beyond the launch's parts gets none (-1)
+__device__ inline Ordered take_part(UpdateWork* w, int parts) {
+    const uint64_t t = atomicAdd((unsigned long long*)&w->tickets, 1ull);
+    const int part = (int)(t & 0xfffff);
+    // the last ticket: the next launch starts at 0
+    if (part == parts - 1) atomicAdd((unsigned long long*)&w->tickets, (1ull << 20) - (uint64_t)parts);
+    return Ordered{((t >> 20) + 1) << 22, part < parts ? part : -1};
+}
+
+__device__ inline void publish_counts(UpdateWork* w, const Ordered& o, uint32_t first, uint32_t second) {
+    __hip_atomic_store(&w->part[o.part], o.tag | second << 11 | first, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    asm volatile("" ::: "memory");  // the store before the polls
+}
+
+// a bound on the wait (about 0.2 s) for handles that a program uses on two
+// streams at once, which it must not: lists of any order and length follow,
+// inside their buffers, and the next k_track_weights sets the tickets right
+constexpr int kMaxPolls = 1 << 18;
+
+// Sums of the published counts of parts [p0, p1), on every lane of the
+// wavefront that calls it: first in the low word, second in the high word.
+__device__ inline uint64_t counts_before(const UpdateWork* w, const Ordered& o, int p0, int p1) {
+    uint64_t sum = 0;
+    for (int p = p0 + (int)(threadIdx.x & 63); p < p1; p += kWave) {
+        uint64_t v;
+        int polls = 0;
+        while ((v = __hip_atomic_load(&w->part[p], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) >> 22 != o.tag >> 22 &&
+               ++polls < kMaxPolls)
+            __builtin_amdgcn_s_sleep(1);
+        sum += (v & 0x7ff) | ((v >> 11) & 0x7ff) << 32;
+    }
+    return wave_sum_u64(sum);
+}
+
+// flagged threads of the wavefronts before this one, and of all 16 (counts
+// per wavefront in LDS)
+__device__ inline int waves_before(const int* cnt, int wave, int* all) {
     int offs = 0, acc = 0;
 #pragma unroll
-    for (int w = 0; w < 16; ++w) {
-        const int c = lds[w];
-        offs += w < wid ? c : 0;
+    for (int q = 0; q < 16; ++q) {
+        const int c = cnt[q];
+        offs += q < wave ? c : 0;
         acc += c;
     }
-    if (threadIdx.x == 0) lds[17] = acc ? (int)atomicAdd(count, (uint32_t)acc) : 0;
-    __syncthreads();
-    return lds[17] + offs + __popcll(m & ((1ull << lane) - 1ull));
+    *all = acc;
+    return offs;
+}
+
+// sample q of a level: whether its depth is valid, and its point
+__device__ inline bool sample_point(const InitStatic& a, const float* depth, int stride, int q, int total, float4* x) {
+    const int su = (a.cam.W + stride - 1) / stride, sv = (a.cam.H + stride - 1) / stride;
+    int uu, vv;
+    if (q >= total || !sample_at(q, su, sv, true, &uu, &vv)) return false;
+    const float z = depth[(int64_t)(vv * stride) * a.cam.W + uu * stride];
+    if (!(z > 0.0f)) return false;
+    *x = unproject_px(a.cam, uu * stride, vv * stride, z);
+    return true;
+}
+
+__device__ inline int level_samples(const InitStatic& a, int l) {
+    return sample_count((a.cam.W + a.stride[l] - 1) / a.stride[l], (a.cam.H + a.stride[l] - 1) / a.stride[l], true);
 }
 
 // Unprojection of the frame at every resolution level, device-state
-// initialisation and the first overlap set (level 0).  Each of a.blocks
-// workgroups takes a contiguous part of every level's samples (8x8-sample
-// tile order) and appends its points; the last one to finish sets the counts.
-// One 640x480 frame at stride 4: 49 us with one workgroup, 8 us with 19.
+// initialisation and the first overlap set (level 0), in 8x8-sample tile
+// order: a workgroup per 1024 samples of a level, or one for all.  One
+// 640x480 frame at stride 4: 49 us with one workgroup, 7 us with 19.
 __device__ void track_init_body(const InitStatic& a, const FrameIn& in, int block) {
-    __shared__ int lds[18], lds_o[18];
+    __shared__ int cnt[17], cnt_o[17];
     __shared__ float A[12];
+    __shared__ Ordered ord;
+    __shared__ uint64_t before;
+    const int tid = (int)threadIdx.x, lane = tid & 63, wave = tid >> 6;
     if (!in.active) {
-        if (threadIdx.x == 0 && block == 0) {
+        if (tid == 0 && block == 0) {
             a.st->stopped = 1;
             a.st->k = 0;
             a.st->n_points = -1;
         }
         return;
     }
-    if (threadIdx.x == 0) {
+    if (tid == 128 && a.blocks > 1) ord = take_part(a.work, a.blocks);
+    if (tid == 0) {
         double Tc[12], Ad[12];
         pose_matrix(in.qc, in.tc, Tc);
         relative_transform(in.Tprev, Tc, Ad);
         for (int i = 0; i < 12; ++i) A[i] = (float)Ad[i];
     }
-    if (threadIdx.x == 64 && block == 0) {
+    if (tid == 64 && block == 0) {
         DevState* s = a.st;
         for (int i = 0; i < 4; ++i) s->qc[i] = in.qc[i];
         for (int i = 0; i < 3; ++i) s->tc[i] = in.tc[i];
@@ -67,50 +125,80 @@ __device__ void track_init_body(const InitStatic& a, const FrameIn& in, int bloc
         s->empty_streak = 0;
         s->have_rho = 0;
         s->status = 0;
+        for (int l = a.levels; l < ROSE_MAX_LEVELS; ++l) s->lvl_points[l] = 0;
     }
     __syncthreads();
     const bool all = (a.flags & ROSE_FLAG_NO_OVERLAP) != 0;
-    for (int l = 0; l < a.levels; ++l) {
-        const int stride = a.stride[l];
-        const int su = (a.cam.W + stride - 1) / stride, sv = (a.cam.H + stride - 1) / stride;
-        const int total = sample_count(su, sv, true), bd = (int)blockDim.x;
-        const int per = (total + a.blocks * bd - 1) / (a.blocks * bd) * bd;  // samples per workgroup
-        const int q1 = min(total, (block + 1) * per);
-        for (int q0 = block * per; q0 < q1; q0 += bd) {
-            const int q = q0 + (int)threadIdx.x;
-            bool keep = false;
-            float4 x = make_float4(0, 0, 0, 0);
-            int uu, vv;
-            if (q < q1 && sample_at(q, su, sv, true, &uu, &vv)) {
-                const int u = uu * stride, v = vv * stride;
-                const float z = in.depth[(int64_t)v * a.cam.W + u];
-                if (z > 0.0f) {
-                    keep = true;
-                    x = unproject_px(a.cam, u, v, z);
+    float4 x = make_float4(0, 0, 0, 0);
+    if (a.blocks == 1) {
+        int any = 0;
+        for (int l = 0; l < a.levels; ++l) {
+            const int total = level_samples(a, l);
+            int m = 0, mo = 0;
+            for (int q0 = 0; q0 < total; q0 += 1024) {
+                const bool keep = sample_point(a, in.depth, a.stride[l], q0 + tid, total, &x);
+                const bool over = l == 0 && keep && (all || overlap_keep(a.cam, A, x));
+                int n, no;
+                const int pos = block_scan_flag(keep, cnt, &n), po = block_scan_flag(over, cnt_o, &no);
+                if (keep) a.pts[a.offset[l] + m + pos] = x;
+                if (over) a.pts_o[mo + po] = x;
+                m += n;
+                mo += no;
+            }
+            any += m > 0;
+            if (tid == 0) {
+                a.st->lvl_points[l] = m;
+                if (l == 0) {
+                    a.st->n_points = m;
+                    a.st->n_overlap = mo;
                 }
             }
-            const int pos = append_positions(keep, &a.work->pts_count[l], lds);
-            if (keep) a.pts[a.offset[l] + pos] = x;
-            if (l == 0) {
-                const bool over = keep && (all || overlap_keep(a.cam, A, x));
-                const int po = append_positions(over, &a.work->overlap_count, lds_o);
-                if (over) a.pts_o[po] = x;
+        }
+        if (tid == 0) a.st->stopped = any == 0 ? 1 : 0;
+        return;
+    }
+    const Ordered o = ord;
+    if (o.part < 0) return;
+    int l = 0, first = 0, total = level_samples(a, 0);  // the part's level, that level's first part
+    while (o.part - first >= (total + 1023) / 1024) {
+        first += (total + 1023) / 1024;
+        total = level_samples(a, ++l);
+    }
+    const bool keep = sample_point(a, in.depth, a.stride[l], (o.part - first) * 1024 + tid, total, &x);
+    const bool over = l == 0 && keep && (all || overlap_keep(a.cam, A, x));
+    const uint64_t bk = __ballot(keep), bo = __ballot(over), below = (1ull << lane) - 1ull;
+    if (lane == 0) {
+        cnt[wave] = __popcll(bk);
+        cnt_o[wave] = __popcll(bo);
+    }
+    __syncthreads();
+    int n, no;
+    const int pos = waves_before(cnt, wave, &n) + __popcll(bk & below);
+    const int po = waves_before(cnt_o, wave, &no) + __popcll(bo & below);
+    if (wave == 0) {
+        if (lane == 0) publish_counts(a.work, o, (uint32_t)n, (uint32_t)no);
+        const uint64_t b = counts_before(a.work, o, first, o.part);
+        if (lane == 0) before = b;
+    }
+    __syncthreads();
+    if (keep) a.pts[a.offset[l] + (int)(uint32_t)before + pos] = x;
+    if (over) a.pts_o[(int)(before >> 32) + po] = x;
+    if (o.part == a.blocks - 1 && wave == 0) {  // the last part: the sizes of all levels
+        int any = 0;
+        for (int k = 0, p = 0; k < a.levels; ++k) {
+            const int np = (level_samples(a, k) + 1023) / 1024;
+            const uint64_t m = counts_before(a.work, o, p, p + np);
+            p += np;
+            any += (uint32_t)m > 0u;
+            if (lane == 0) {
+                a.st->lvl_points[k] = (int)(uint32_t)m;
+                if (k == 0) {
+                    a.st->n_points = (int)(uint32_t)m;
+                    a.st->n_overlap = (int)(m >> 32);
+                }
             }
         }
-    }
-    if (threadIdx.x == 0 && atomicAdd(&a.work->ticket, 1u) == (uint32_t)a.blocks - 1u) {
-        // every workgroup's counts are in (each had its atomics' results
-        // before it took its ticket)
-        uint32_t any = 0;
-        for (int l = 0; l < ROSE_MAX_LEVELS; ++l) {
-            const uint32_t ml = atomicExch(&a.work->pts_count[l], 0u);
-            a.st->lvl_points[l] = (int)ml;
-            if (l == 0) a.st->n_points = (int)ml;
-            any += ml;
-        }
-        a.st->n_overlap = (int)atomicExch(&a.work->overlap_count, 0u);
-        a.st->stopped = any == 0 ? 1 : 0;
-        atomicExch(&a.work->ticket, 0u);
+        if (lane == 0) a.st->stopped = any == 0 ? 1 : 0;
     }
 }
 
@@ -197,6 +285,7 @@ __device__ void track_weights_body(const UpdateArgs& a, int g) {
     if (g == 0)
         for (int i = threadIdx.x; i < kSnapWords; i += kWeightThreads)
             ((uint32_t*)&a.work->snap)[i] = ((const uint32_t*)st)[i];
+    if (g == 0 && threadIdx.x == 448) atomicAnd((unsigned long long*)&a.work->tickets, ~0xfffffull);
     if (st->stopped || g * kWave >= a.n) return;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int nO = st->n_overlap, i0 = g * kWave;
@@ -283,11 +372,10 @@ __device__ inline void pst_update(const UpdateArgs& a, StepState& s, const doubl
 // 1024 in increasing j, over the wavefront by butterfly, over the wavefronts
 // in turn) and takes the same step from the same copy of the state, which is
 // not worth a launch of its own; then it tests 1024 points against the new
-// centre and appends those of the next overlap set.  Workgroup 0 writes the
-// state, the last one to finish the set's size.  With one workgroup the
-// points keep their order.  512^3 frame of 10240 particles and 19200 points:
-// both launches 18 us per iteration, against 32 us for a reduction launch and
-// one workgroup that did the rest; the 32 frames of a batch: 19 against 36 us.
+// centre and writes those of the next overlap set, in the points' order
+// (Ordered).  Workgroup 0 writes the state, the last part's the set's size.  512^3 frame of 10240 particles and 19200 points:
+// both launches 19 us per iteration, against 32 us for a reduction launch and
+// one workgroup that did the rest; the 32 frames of a batch: 21 against 36 us.
 __device__ void track_step_body(const UpdateArgs& a, int block) {
     __shared__ int lds[18];
     __shared__ double red[16][9], tot[9];
@@ -299,10 +387,10 @@ __device__ void track_step_body(const UpdateArgs& a, int block) {
     __shared__ StepState next;
     const int tid = (int)threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const UpdateWork& w = *a.work;
-    const int j = block * 1024 + tid;
-    // read before the sums and the step, whose latency these loads overlap
+    __shared__ Ordered ord;
+    // read before the sums, whose latency this load overlaps
     const uint32_t snap = ((const uint32_t*)&w.snap)[min(tid, kSnapWords - 1)];
-    const float4 x = a.pts[min(j, a.pts_cap - 1)];
+    if (tid == 960 && a.blocks > 1) ord = take_part(a.work, a.blocks);
     double v9[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
     double r6[6];
 #pragma unroll
@@ -339,6 +427,9 @@ __device__ void track_step_body(const UpdateArgs& a, int block) {
     if (tid == 0) centre = wr[0].y;  // the likelihood of particle 0
     __syncthreads();
     if (s.stopped) return;  // (the terms are not this iteration's)
+    // the part's point, read before the step that its latency overlaps (a
+    // single workgroup has no part and reads all points in overlap_compact)
+    const float4 x = a.pts[min(a.blocks > 1 ? max(ord.part, 0) * 1024 + tid : 0, a.pts_cap - 1)];
     if (tid < 9) {
         double v = 0.0;
         for (int q = 0; q < 16; ++q) v += red[q][tid];
@@ -411,23 +502,20 @@ __device__ void track_step_body(const UpdateArgs& a, int block) {
         if (tid == 0) a.st->n_overlap = n;
         return;
     }
-    const bool keep = j < m && (all || overlap_keep(a.cam, A, x));
+    const Ordered o = ord;
+    if (o.part < 0) return;
+    const bool keep = o.part * 1024 + tid < m && (all || overlap_keep(a.cam, A, x));
     const uint64_t ball = __ballot(keep);
     if (lane == 0) lds[wave] = __popcll(ball);
     __syncthreads();
-    int offs = 0, acc = 0;  // kept points of the wavefronts before this one, of all
-#pragma unroll
-    for (int q = 0; q < 16; ++q) {
-        const int c = lds[q];
-        offs += q < wave ? c : 0;
-        acc += c;
-    }
-    if (tid == 0) {
-        const uint64_t before = atomicAdd((unsigned long long*)&a.work->pack, (1ull << 32) | (uint32_t)acc);
-        lds[17] = (int)(uint32_t)before;
-        if ((before >> 32) == (uint64_t)a.blocks - 1u) {
-            a.st->n_overlap = (int)(uint32_t)before + acc;
-            atomicExch((unsigned long long*)&a.work->pack, 0ull);
+    int acc;
+    const int offs = waves_before(lds, wave, &acc);
+    if (wave == 0) {
+        if (lane == 0) publish_counts(a.work, o, (uint32_t)acc, 0u);
+        const int before = (int)(uint32_t)counts_before(a.work, o, 0, o.part);
+        if (lane == 0) {
+            lds[17] = before;
+            if (o.part == a.blocks - 1) a.st->n_overlap = before + acc;
         }
     }
     __syncthreads();
@@ -644,7 +732,6 @@ rose_status pso_track_frame(rose_tsdf* h, const float* depth_dev, const float* p
 
     ia.st = h->st;
     ia.work = work_of(h->st);
-    ia.blocks = compact_blocks(mmax_all, p->flags);
     ia.cam = to_cam(cam, prev_depth_dev);
     ia.flags = p->flags;
     ia.pts = h->pts;
@@ -661,6 +748,7 @@ rose_status pso_track_frame(rose_tsdf* h, const float* depth_dev, const float* p
     const int32_t* lv_order[ROSE_MAX_LEVELS] = {nullptr, nullptr, nullptr, nullptr};
     for (int l = 0; l < L; ++l)
         if ((g = particle_order(h, pst_dev, lv_n[l], s, &lv_order[l])) != ROSE_OK) return g;
+    ia.blocks = init_blocks(ia);
     if ((g = launch_track_init(ia, fin, s)) != ROSE_OK) return g;
 
     FitLaunch fl{};
@@ -705,7 +793,7 @@ rose_status pso_track_frame(rose_tsdf* h, const float* depth_dev, const float* p
         ua.pts = h->pts + lv_off[ln];
         ua.next_level = ln;
         ua.pts_cap = (int32_t)(lv_off[ln + 1] - lv_off[ln]);
-        ua.blocks = compact_blocks(ua.pts_cap, p->flags);
+        ua.blocks = step_blocks(ua.pts_cap);
         tok_fit[k] = prof_begin(PROF_FITNESS, s);
         if ((g = launch_fitness(fl, s)) != ROSE_OK) return g;
         prof_end(tok_fit[k], s, 0.0);
@@ -1059,7 +1147,6 @@ rose_status pso_batch_create(int32_t count, rose_tsdf* const* tsdfs, const rose_
         ia = InitStatic{};
         ia.st = h->st;
         ia.work = work_of(h->st);
-        ia.blocks = compact_blocks(mmax, p.flags);
         ia.cam = to_cam(&cams[i]);
         ia.levels = 1;
         ia.flags = p.flags;
@@ -1069,9 +1156,10 @@ rose_status pso_batch_create(int32_t count, rose_tsdf* const* tsdfs, const rose_
         UpdateArgs& ua = upd[i];
         ua.st = h->st;
         ua.work = ia.work;
-        ua.blocks = ia.blocks;
+        ia.blocks = init_blocks(ia);
+        ua.blocks = step_blocks(mmax);
         ua.pts_cap = (int32_t)mmax;
-        b->max_blocks = std::max(b->max_blocks, ua.blocks);
+        b->max_blocks = std::max({b->max_blocks, ia.blocks, ua.blocks});
         ua.cam = to_cam(&cams[i]);
         ua.pst = pst_devs[i];
         ua.partial = h->partial;

@@ -121,14 +121,18 @@ __device__ inline int overlap_compact(const Cam& c, const float* A, bool all, co
     return base;
 }
 
-// Scratch of the per-iteration update, behind each handle's DevState in one
-// allocation (track_memory).  The counters are 0 whenever no frame is being
-// tracked: the last workgroup that uses them resets them.
+// The frame setup and the update write lists of points in index order from
+// many workgroups: 1024 samples or points each, in the order of their tickets
+// (Ordered, track.hip).  Lists of more than kMaxParts parts are written by one
+// workgroup.
+constexpr int kMaxParts = 4096;
+
+// Scratch of the frame setup and the update, behind each handle's DevState in
+// one allocation (track_memory).
 struct UpdateWork {
-    uint64_t pack;                          // compaction: workgroups done << 32 | points kept so far
-    uint32_t pts_count[ROSE_MAX_LEVELS];    // init: valid samples so far, per level
-    uint32_t overlap_count, ticket;         // init: overlap points so far, workgroups done
-    DevState snap;                          // the state before the update (fields up to lvl_points)
+    uint64_t tickets;          // launches that took tickets << 20 | tickets taken in this one
+    uint64_t part[kMaxParts];  // (launch + 1) << 22 | second count << 11 | first count (at most 1024 each)
+    DevState snap;             // the state before the update (fields up to lvl_points)
 };
 
 inline UpdateWork* work_of(DevState* st) { return (UpdateWork*)((char*)st + (sizeof(DevState) + 255) / 256 * 256); }
@@ -152,11 +156,10 @@ inline rose_status track_memory(rose_tsdf* h) {
 // comparison optimisers), then an APS weight and likelihood each.
 inline int64_t fitness_floats(int64_t n) { return (n + 3) / 4 * 4 + 4 * n; }
 
-// Workgroups of 1024 points for the compaction of up to `points` points: one
-// where the order of the points has to be kept (the no-Kahan ablation, whose
-// binary32 sums depend on it; the sums on the grid do not).
-inline int compact_blocks(int64_t points, int flags) {
-    return (flags & ROSE_FLAG_NO_KAHAN) ? 1 : (int)std::max<int64_t>((points + 1023) / 1024, 1);
+// workgroups of the step for a level of up to `points` points
+inline int step_blocks(int64_t points) {
+    const int64_t b = (points + 1023) / 1024;
+    return b <= kMaxParts ? (int)std::max<int64_t>(b, 1) : 1;
 }
 
 struct InitStatic {
@@ -171,6 +174,16 @@ struct InitStatic {
     float4* pts;
     float4* pts_o;
 };
+
+// workgroups of the init launch: 1024 padded samples of one level each
+inline int init_blocks(const InitStatic& a) {
+    int64_t b = 0;
+    for (int l = 0; l < a.levels; ++l) {
+        const int su = (a.cam.W + a.stride[l] - 1) / a.stride[l], sv = (a.cam.H + a.stride[l] - 1) / a.stride[l];
+        b += ((int64_t)((su + 7) / 8) * ((sv + 7) / 8) * 64 + 1023) / 1024;
+    }
+    return b <= kMaxParts ? (int)std::max<int64_t>(b, 1) : 1;
+}
 
 struct UpdateArgs {
     DevState* st;

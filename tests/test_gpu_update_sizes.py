@@ -1,8 +1,8 @@
 """The per-iteration update at the edges of its launches: particle counts
 around the 64 that one workgroup sums and point counts around the 1024 that
-one workgroup tests (one workgroup keeps the order of the points, several
-append to the list as they come), for one and several resolution levels and
-with every point kept.  The frame equals the oracle's: valid points, overlap
+one workgroup tests (several workgroups write their parts of the list in
+order, one at stride 6 the whole list), for one and several resolution levels
+and with every point kept.  The frame equals the oracle's: valid points, overlap
 and APS sizes per iteration, pose; a second run of the same frame equals the
 first bit for bit."""
 import numpy as np
@@ -44,7 +44,7 @@ def _frame(w, points, stride):
 @pytest.mark.parametrize("n,points,stride,flags,levels", [
     (2, 1, 3, 0, None), (63, 1023, 3, 0, None), (64, 1024, 3, 0, None), (65, 1025, 3, 0, None),
     (1025, 2048, 2, 0, None), (1100, 2049, 2, 0, None), (1088, 4800, 2, 1, None), (500, 19200, 1, 0, None),
-    (900, 4000, 2, 0, [(900, 4), (300, 2), (65, 3)]), (300, 2160, 3, 2, None)])
+    (900, 4000, 2, 0, [(900, 4), (300, 2), (65, 3)]), (300, 2160, 3, 2, None), (200, 500, 6, 0, None)])
 def test_update_sizes(orc, small, n, points, stride, flags, levels):
     from paper_2105_05600_amd import rose
     w, vol, psi, pst = small
