@@ -467,10 +467,10 @@ rose_status pso_track_frame_learned(rose_tsdf* h, const float* depth_dev, const 
  * particle count and parameters) tracked in lockstep, one frame step per
  * pso_batch_track call, with the same per-sequence semantics as
  * pso_track_frame.  Per frame step the device work is: one unprojection /
- * overlap launch (one workgroup per sequence), then per iteration one
+ * overlap launch (a column of workgroups per sequence), then per iteration one
  * persistent fitness launch per group over the sequences that share it, the
  * fitness launches of pso_track_frame for each sequence that has its own
- * (see rose_batch_set_own_launch), one slice-reduction launch and one update
+ * (see rose_batch_set_own_launch), one launch for the APS terms and one update
  * launch, then one launch copying the states to pinned host memory; with
  * use_graph != 0 and a non-null stream it is captured into a HIP graph on
  * the first call and replayed afterwards (new inputs are read from pinned

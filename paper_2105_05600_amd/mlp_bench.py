@@ -1,5 +1,5 @@
-"""Throughput of the proposal network's matrix-core kernels (k_gemm_bf16 and
-the elementwise kernels around it) at the sizes the learned proposal uses:
+"""Throughput of the proposal network's matrix-core kernels (k_gemm_tile,
+k_gemm_small and the elementwise kernels around them) at the sizes the learned proposal uses:
 one inference per sequence (B = 1, and 32 for a batched frame step), a
 training step of B = 1024 samples (forward, NLL loss and gradients, Adam),
 and one large GEMM (4096^3) for the kernel itself away from the latency of
@@ -95,7 +95,7 @@ def summary(trace_dir: str, bench_json: str, command: str) -> str:
     rows.sort(key=lambda r: -float(r["TotalDurationNs"]))
     with open(bench_json) as f:
         bench = json.loads(f.read().strip().splitlines()[-1])
-    lines = ["# k_gemm_bf16 and the proposal network's kernels (forward, training step, 4096^3 GEMM)", "",
+    lines = ["# k_gemm_tile, k_gemm_small and the proposal network's kernels (forward, training step, 4096^3 GEMM)", "",
              "rocprofv3 kernel-trace statistics of one mlp_bench.py run (MI355X, gfx950).", "",
              "Command (repository root, after `cd /tmp && export TMPDIR=/tmp` and back):", "", f"    {command}", "",
              "| kernel | calls | avg us | min us | max us | share % |", "|---|---|---|---|---|---|"]
@@ -103,7 +103,7 @@ def summary(trace_dir: str, bench_json: str, command: str) -> str:
         name = r["Name"] if len(r["Name"]) <= 90 else r["Name"][:87] + "..."
         lines.append(f"| `{name}` | {r['Calls']} | {float(r['AverageNs']) / 1e3:.1f} | {float(r['MinNs']) / 1e3:.1f} | "
                      f"{float(r['MaxNs']) / 1e3:.1f} | {float(r['Percentage']):.2f} |")
-    lines += ["", "The run's own timing (HIP events; TFLOP/s of the GEMM work, fraction of the 2.5 PFLOP/s dense "
+    lines += ["", "The run's own timing (HIP events, with the tracer's cost per launch; TFLOP/s of the GEMM work, fraction of the 2.5 PFLOP/s dense "
               "BF16 peak):", ""]
     for k, v in bench.items():
         if isinstance(v, dict) and "tflops" in v:
