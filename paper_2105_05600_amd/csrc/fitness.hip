@@ -34,19 +34,23 @@ __device__ inline uint32_t elem_bytes() {
 struct PsiBuf {
     __amdgpu_buffer_rsrc_t r;
     __amdgpu_buffer_rsrc_t ones;
-    __amdgpu_buffer_rsrc_t pair;  // 16-bit formats: psi from the 4-byte boundary at or below it,
-    uint32_t mis;                 // and its offset from there
+    // 16-bit formats: psi from the 4-byte boundary at or below it to the one
+    // at or above its end (a load's range is checked a dword at a time: a last
+    // voxel in a dword only half inside would read 0), and its offset from there
+    __amdgpu_buffer_rsrc_t pair;
+    uint32_t mis;
 };
 
 template <int FMT>
 __device__ inline PsiBuf psi_buffer(const Grid& g) {
     const uint32_t bytes = (uint32_t)g.nx * (uint32_t)g.ny * (uint32_t)g.nz * elem_bytes<FMT>();
     const uint32_t words = ((uint32_t)g.nbx * (uint32_t)g.nby * (uint32_t)g.nbz + 31u) / 32u;
-    // dword 3 of a raw (stride 0) buffer resource on gfx9-family targets
     const uint32_t mis = (uint32_t)(uintptr_t)g.psi & 3u;
+    // dword 3 of a raw (stride 0) buffer resource on gfx9-family targets
     return PsiBuf{__builtin_amdgcn_make_buffer_rsrc(g.psi, (short)0, (int)bytes, 0x00020000),
                   __builtin_amdgcn_make_buffer_rsrc(g.ones, (short)0, (int)(4u * words), 0x00020000),
-                  __builtin_amdgcn_make_buffer_rsrc((char*)g.psi - mis, (short)0, (int)(bytes + mis), 0x00020000),
+                  __builtin_amdgcn_make_buffer_rsrc((char*)g.psi - mis, (short)0, (int)((bytes + mis + 3u) & ~3u),
+                                                    0x00020000),
                   mis};
 }
 
