@@ -61,3 +61,18 @@ def test_wide_export_round_trip(wide):
     assert np.array_equal(g[960:1024, 448:576, 448:576].view(np.uint32),
                           psi[960:1024, 448:576, 448:576].view(np.uint32))
     assert np.all(g[:960:97] == 1.0)
+
+
+@pytest.mark.parametrize("w,h", [(40, 30), (140, 110), (520, 510)])
+def test_wide_raycast(orc, wide, w, h):
+    """1, 4 and 16 pixels per wavefront, marching through the first 4 GB into the random block: the oracle's bits."""
+    rose, vol, psi = wide
+
+    class K:
+        width, height, fx, fy, cx, cy = w, h, 3.0 * w, 3.0 * w, w / 2 - 0.5, h / 2 - 0.5
+
+    q, t = [1.0, 0.0, 0.0, 0.0], [5.13, 5.11, 7.9]
+    g = rose.raycast(vol, q, t, K, near=0.2, far=2.6, step=VOX / 2).cpu().numpy()
+    o = orc.raycast(psi, VOX, np.zeros(3), np.array(q), np.array(t), K, near=0.2, far=2.6, step=VOX / 2)
+    assert np.array_equal(g, np.asarray(o, np.float32).reshape(g.shape))
+    assert float((g > 0).mean()) > 0.5
