@@ -320,7 +320,7 @@ typedef struct {
     int32_t iters;          /* iterations run */
     int32_t n_points;       /* valid subsampled points (of level 0 under a multi-resolution schedule) */
     int32_t n_overlap_last; /* |O_k| of the last iteration */
-    int32_t status;         /* pso_batch_track: per-sequence status (ROSE_E_STATE: no valid depth) */
+    int32_t status;         /* pso_batch_track: per-sequence status (ROSE_E_STATE as for pso_track_frame) */
     int32_t aps_size[ROSE_MAX_ITERS];
     int32_t n_overlap[ROSE_MAX_ITERS]; /* |O_k| per iteration */
     double rho_iter[ROSE_MAX_ITERS];   /* rho~ per iteration (rho of the centre when the APS is empty) */
@@ -354,7 +354,8 @@ typedef struct {
  * depend on that order.
  * state->tsdf_built == 0: no fitness is evaluated; r_1 = beta r_0 +
  * (1-beta) 0.5 and the pose is kept.  Returns ROSE_E_STATE (state
- * unchanged) when the frame has no valid point.
+ * unchanged) when the frame has no valid point, and when another stream's
+ * use of the handle during the call left the point lists incomplete.
  * Limits: n_particles <= ROSE_MAX_PARTICLES; image <= ROSE_MAX_IMAGE_PIXELS.
  * A handle must not be used by two streams at once. */
 rose_status pso_track_frame(rose_tsdf* h, const float* depth_dev, const float* prev_depth_dev,

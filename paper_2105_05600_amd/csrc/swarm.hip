@@ -406,6 +406,7 @@ static rose_status swarm_track(rose_tsdf* h, const float* depth_dev, const rose_
     ROSE_CHECK_HIP(hipMemcpyAsync(h->st_host, h->st, sizeof(DevState), hipMemcpyDeviceToHost, s));
     ROSE_CHECK_HIP(hipStreamSynchronize(s));
     const DevState& ch = *h->st_host;
+    if ((g = list_status(h, ch, s, who)) != ROSE_OK) return g;
     if (ch.n_points == 0) {
         set_error("%s: the frame has no valid depth sample", who);
         return ROSE_E_STATE;

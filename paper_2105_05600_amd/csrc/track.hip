@@ -17,8 +17,8 @@ namespace rose {
 // counts and then waits for theirs, and every such wait ends.  The order is
 // what makes the slices of the fitness kernels compact (appending the parts
 // as they come cost the 512^3 sequence 36 % more HBM reads and 8 % of the
-// fitness time).  The counts travel in one word with the launch they are of,
-// so nothing has to be cleared.
+// fitness time).  The counts travel in one word with the launch they are of
+// (ordered.h), so nothing has to be cleared.
 struct Ordered {
     uint64_t tag;  // this launch
     int part;
@@ -30,32 +30,37 @@ __device__ inline Ordered take_part(UpdateWork* w, int parts) {
     const int part = (int)(t & 0xfffff);
     // the last ticket: the next launch starts at 0
     if (part == parts - 1) atomicAdd((unsigned long long*)&w->tickets, (1ull << 20) - (uint64_t)parts);
-    return Ordered{((t >> 20) + 1) << 22, part < parts ? part : -1};
+    return Ordered{launch_tag(t >> 20), part < parts ? part : -1};
 }
 
 __device__ inline void publish_counts(UpdateWork* w, const Ordered& o, uint32_t first, uint32_t second) {
-    __hip_atomic_store(&w->part[o.part], o.tag | second << 11 | first, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(&w->part[o.part], part_word(o.tag, first, second), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     asm volatile("" ::: "memory");  // the store before the polls
 }
 
-// a bound on the wait (about 0.2 s) for handles that a program uses on two
-// streams at once, which it must not: lists of any order and length follow,
-// inside their buffers, and the next k_track_weights sets the tickets right
+// A bound on the wait (0.07 s), for handles that a program uses on two
+// streams at once, which it must not: a part that finds no predecessor's
+// count, or no part left for it, writes nothing and sets DevState::status.
+// Positions and sizes stay inside the lists whatever the counts (list_slot,
+// list_size), and the host turns the status into an error and clears the
+// tickets (list_status).
 constexpr int kMaxPolls = 1 << 18;
 
-// Sums of the published counts of parts [p0, p1), on every lane of the
-// wavefront that calls it: first in the low word, second in the high word.
+// Sums of the published counts of parts [p0, p1) on every lane of the
+// wavefront that calls it (part_counts), or kCountsLost.
 __device__ inline uint64_t counts_before(const UpdateWork* w, const Ordered& o, int p0, int p1) {
     uint64_t sum = 0;
+    bool lost = false;
     for (int p = p0 + (int)(threadIdx.x & 63); p < p1; p += kWave) {
         uint64_t v;
         int polls = 0;
-        while ((v = __hip_atomic_load(&w->part[p], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) >> 22 != o.tag >> 22 &&
-               ++polls < kMaxPolls)
+        while (!part_published(v = __hip_atomic_load(&w->part[p], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT), o.tag) &&
+               !(lost = ++polls >= kMaxPolls))
             __builtin_amdgcn_s_sleep(1);
-        sum += (v & 0x7ff) | ((v >> 11) & 0x7ff) << 32;
+        if (lost) break;
+        sum += part_counts(v);
     }
-    return wave_sum_u64(sum);
+    return __any(lost) ? kCountsLost : wave_sum_u64(sum);
 }
 
 // flagged threads of the wavefronts before this one, and of all 16 (counts
@@ -85,6 +90,11 @@ __device__ inline bool sample_point(const InitStatic& a, const float* depth, int
 
 __device__ inline int level_samples(const InitStatic& a, int l) {
     return sample_count((a.cam.W + a.stride[l] - 1) / a.stride[l], (a.cam.H + a.stride[l] - 1) / a.stride[l], true);
+}
+
+// points that a level's list has room for
+__device__ inline int level_capacity(const InitStatic& a, int l) {
+    return ((a.cam.W + a.stride[l] - 1) / a.stride[l]) * ((a.cam.H + a.stride[l] - 1) / a.stride[l]);
 }
 
 // Unprojection of the frame at every resolution level, device-state
@@ -124,7 +134,6 @@ __device__ void track_init_body(const InitStatic& a, const FrameIn& in, int bloc
         s->k = 0;
         s->empty_streak = 0;
         s->have_rho = 0;
-        s->status = 0;
         for (int l = a.levels; l < ROSE_MAX_LEVELS; ++l) s->lvl_points[l] = 0;
     }
     __syncthreads();
@@ -158,7 +167,10 @@ __device__ void track_init_body(const InitStatic& a, const FrameIn& in, int bloc
         return;
     }
     const Ordered o = ord;
-    if (o.part < 0) return;
+    if (o.part < 0) {
+        if (tid == 0) a.st->status = 1;
+        return;
+    }
     int l = 0, first = 0, total = level_samples(a, 0);  // the part's level, that level's first part
     while (o.part - first >= (total + 1023) / 1024) {
         first += (total + 1023) / 1024;
@@ -178,23 +190,30 @@ __device__ void track_init_body(const InitStatic& a, const FrameIn& in, int bloc
     if (wave == 0) {
         if (lane == 0) publish_counts(a.work, o, (uint32_t)n, (uint32_t)no);
         const uint64_t b = counts_before(a.work, o, first, o.part);
-        if (lane == 0) before = b;
+        if (lane == 0) {
+            before = b;
+            if (b == kCountsLost) a.st->status = 1;
+        }
     }
     __syncthreads();
-    if (keep) a.pts[a.offset[l] + (int)(uint32_t)before + pos] = x;
-    if (over) a.pts_o[(int)(before >> 32) + po] = x;
+    const int cap = level_capacity(a, l);
+    const int at = keep ? list_slot(before, 0, pos, cap) : -1, at_o = over ? list_slot(before, 1, po, cap) : -1;
+    if (at >= 0) a.pts[a.offset[l] + at] = x;
+    if (at_o >= 0) a.pts_o[at_o] = x;
     if (o.part == a.blocks - 1 && wave == 0) {  // the last part: the sizes of all levels
         int any = 0;
         for (int k = 0, p = 0; k < a.levels; ++k) {
             const int np = (level_samples(a, k) + 1023) / 1024;
             const uint64_t m = counts_before(a.work, o, p, p + np);
             p += np;
-            any += (uint32_t)m > 0u;
+            const int n_k = list_size(m, 0, level_capacity(a, k));
+            any += n_k > 0;
             if (lane == 0) {
-                a.st->lvl_points[k] = (int)(uint32_t)m;
+                if (m == kCountsLost) a.st->status = 1;
+                a.st->lvl_points[k] = n_k;
                 if (k == 0) {
-                    a.st->n_points = (int)(uint32_t)m;
-                    a.st->n_overlap = (int)(m >> 32);
+                    a.st->n_points = n_k;
+                    a.st->n_overlap = list_size(m, 1, level_capacity(a, 0));
                 }
             }
         }
@@ -377,7 +396,8 @@ __device__ inline void pst_update(const UpdateArgs& a, StepState& s, const doubl
 // both launches 19 us per iteration, against 32 us for a reduction launch and
 // one workgroup that did the rest; the 32 frames of a batch: 21 against 36 us.
 __device__ void track_step_body(const UpdateArgs& a, int block) {
-    __shared__ int lds[18];
+    __shared__ int lds[17];
+    __shared__ uint64_t before;
     __shared__ double red[16][9], tot[9];
     __shared__ float A[12];
     __shared__ DevState s;
@@ -495,7 +515,7 @@ __device__ void track_step_body(const UpdateArgs& a, int block) {
         }
     }
     if (!go_on) return;
-    const int m = s.lvl_points[a.next_level];
+    const int m = min(s.lvl_points[a.next_level], a.pts_cap);
     const bool all = (a.flags & ROSE_FLAG_NO_OVERLAP) != 0;
     if (a.blocks == 1) {
         const int n = overlap_compact(a.cam, A, all, a.pts, m, a.pts_o, lds);
@@ -503,7 +523,10 @@ __device__ void track_step_body(const UpdateArgs& a, int block) {
         return;
     }
     const Ordered o = ord;
-    if (o.part < 0) return;
+    if (o.part < 0) {
+        if (tid == 0) a.st->status = 1;
+        return;
+    }
     const bool keep = o.part * 1024 + tid < m && (all || overlap_keep(a.cam, A, x));
     const uint64_t ball = __ballot(keep);
     if (lane == 0) lds[wave] = __popcll(ball);
@@ -512,14 +535,17 @@ __device__ void track_step_body(const UpdateArgs& a, int block) {
     const int offs = waves_before(lds, wave, &acc);
     if (wave == 0) {
         if (lane == 0) publish_counts(a.work, o, (uint32_t)acc, 0u);
-        const int before = (int)(uint32_t)counts_before(a.work, o, 0, o.part);
+        const uint64_t b = counts_before(a.work, o, 0, o.part);
         if (lane == 0) {
-            lds[17] = before;
-            if (o.part == a.blocks - 1) a.st->n_overlap = before + acc;
+            before = b;
+            if (b == kCountsLost) a.st->status = 1;
+            if (o.part == a.blocks - 1)
+                a.st->n_overlap = list_size(b == kCountsLost ? b : b + (uint64_t)acc, 0, a.pts_cap);
         }
     }
     __syncthreads();
-    if (keep) a.pts_o[lds[17] + offs + __popcll(ball & ((1ull << lane) - 1ull))] = x;
+    const int at = keep ? list_slot(before, 0, offs + __popcll(ball & ((1ull << lane) - 1ull)), a.pts_cap) : -1;
+    if (at >= 0) a.pts_o[at] = x;
 }
 
 __global__ __launch_bounds__(1024) void k_track_step(UpdateArgs a) { track_step_body(a, blockIdx.x); }
@@ -806,6 +832,7 @@ rose_status pso_track_frame(rose_tsdf* h, const float* depth_dev, const float* p
     ROSE_CHECK_HIP(hipMemcpyAsync(h->st_host, h->st, sizeof(DevState), hipMemcpyDeviceToHost, s));
     ROSE_CHECK_HIP(hipStreamSynchronize(s));
     const DevState& r = *h->st_host;
+    if ((g = list_status(h, r, s, "pso_track_frame")) != ROSE_OK) return g;
     for (int k = 0; k < p->max_iters; ++k)
         prof_set_evals(tok_fit[k], k < r.k ? (double)lv_n[k % L] * (double)r.n_overlap_iter[k] : 0.0);
     int64_t any = 0;
@@ -1339,11 +1366,13 @@ static rose_status batch_track_impl(rose_batch* b, const float* const* depth_dev
         if (!b->in_host[i].active) continue;
         const DevState& r = b->out_host[i];
         rose_track_state& st = states[i];
+        rose_status lists = list_status(b->h[i], r, s, "pso_batch_track");
+        if (lists == ROSE_OK && r.n_points == 0) lists = ROSE_E_STATE;
         if (stats) {
             memset(&stats[i], 0, sizeof(rose_track_stats));
-            stats[i].status = (r.n_points == 0) ? ROSE_E_STATE : ROSE_OK;
+            stats[i].status = lists;
         }
-        if (r.n_points == 0) continue;  // no valid depth: state unchanged
+        if (lists != ROSE_OK) continue;  // no valid depth, or an error: state unchanged
         for (int k = 0; k < 4; ++k) st.pose.q[k] = r.qc[k];
         for (int k = 0; k < 3; ++k) st.pose.t[k] = r.tc[k];
         for (int d = 0; d < 6; ++d) st.r[d] = r.r1[d];

@@ -6,6 +6,7 @@
 #include <algorithm>
 
 #include "common.h"
+#include "ordered.h"
 
 namespace rose {
 
@@ -131,25 +132,37 @@ constexpr int kMaxParts = 4096;
 // one allocation (track_memory).
 struct UpdateWork {
     uint64_t tickets;          // launches that took tickets << 20 | tickets taken in this one
-    uint64_t part[kMaxParts];  // (launch + 1) << 22 | second count << 11 | first count (at most 1024 each)
+    uint64_t part[kMaxParts];  // part_word of each part
     DevState snap;             // the state before the update (fields up to lvl_points)
 };
 
 inline UpdateWork* work_of(DevState* st) { return (UpdateWork*)((char*)st + (sizeof(DevState) + 255) / 256 * 256); }
 
+constexpr size_t kTrackBytes = (sizeof(DevState) + 255) / 256 * 256 + sizeof(UpdateWork);
+
 // a handle's device state and update scratch, allocated on first use
 inline rose_status track_memory(rose_tsdf* h) {
     if (h->st) return ROSE_OK;
-    const size_t bytes = (sizeof(DevState) + 255) / 256 * 256 + sizeof(UpdateWork);
     void* p = nullptr;
-    ROSE_CHECK_HIP(hipMalloc(&p, bytes));
-    if (hipMemset(p, 0, bytes) != hipSuccess || hipDeviceSynchronize() != hipSuccess) {
+    ROSE_CHECK_HIP(hipMalloc(&p, kTrackBytes));
+    if (hipMemset(p, 0, kTrackBytes) != hipSuccess || hipDeviceSynchronize() != hipSuccess) {
         (void)hipFree(p);
-        set_error("track state: clearing %zu bytes failed", bytes);
+        set_error("track state: clearing %zu bytes failed", kTrackBytes);
         return ROSE_E_DEVICE;
     }
     h->st = (DevState*)p;
     return ROSE_OK;
+}
+
+// The status of a finished frame's point lists (r: the handle's state, copied
+// to the host).  Lists that a second stream's use of the handle left
+// incomplete are an error, after which the scratch is as it was allocated.
+inline rose_status list_status(rose_tsdf* h, const DevState& r, hipStream_t s, const char* who) {
+    if (r.status == 0) return ROSE_OK;
+    ROSE_CHECK_HIP(hipMemsetAsync(h->st, 0, kTrackBytes, s));
+    ROSE_CHECK_HIP(hipStreamSynchronize(s));
+    set_error("%s: the handle was used on another stream during the call", who);
+    return ROSE_E_STATE;
 }
 
 // Floats of a handle's F buffer for n particles: their fitness values (the
