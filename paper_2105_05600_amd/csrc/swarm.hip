@@ -289,7 +289,7 @@ static rose_status swarm_track(rose_tsdf* h, const float* depth_dev, const rose_
     if ((g = grow(&h->pts_o, &h->cap_points_o, mmax)) != ROSE_OK) return g;
     if ((g = grow(&h->partial, &h->cap_partial, (int64_t)n * splits * kPartSub)) != ROSE_OK) return g;
     if ((g = grow(&h->F, &h->cap_particles, (int64_t)n)) != ROSE_OK) return g;
-    if ((g = track_memory(h)) != ROSE_OK) return g;
+    if ((g = track_memory(h, s)) != ROSE_OK) return g;
     if (!h->st_host) ROSE_CHECK_HIP(hipHostMalloc(&h->st_host, sizeof(DevState), hipHostMallocDefault));
     if (h->cap_swarm < n || !h->sw_x) {
         int64_t cap = 0;

@@ -753,7 +753,7 @@ rose_status pso_track_frame(rose_tsdf* h, const float* depth_dev, const float* p
     if ((g = grow(&h->pts_o, &h->cap_points_o, mmax_all)) != ROSE_OK) return g;
     if ((g = grow(&h->partial, &h->cap_partial, partial_need)) != ROSE_OK) return g;
     if ((g = grow(&h->F, &h->cap_particles, fitness_floats(n_particles))) != ROSE_OK) return g;
-    if ((g = track_memory(h)) != ROSE_OK) return g;
+    if ((g = track_memory(h, s)) != ROSE_OK) return g;
     if (!h->st_host) ROSE_CHECK_HIP(hipHostMalloc(&h->st_host, sizeof(DevState), hipHostMallocDefault));
 
     ia.st = h->st;
@@ -1146,7 +1146,7 @@ rose_status pso_batch_create(int32_t count, rose_tsdf* const* tsdfs, const rose_
         if ((g = grow(&h->pts_o, &h->cap_points_o, mmax)) != ROSE_OK) break;
         if ((g = grow(&h->partial, &h->cap_partial, (int64_t)n_particles[i] * splits * kPartSub)) != ROSE_OK) break;
         if ((g = grow(&h->F, &h->cap_particles, fitness_floats(n_particles[i]))) != ROSE_OK) break;
-        if ((g = track_memory(h)) != ROSE_OK) break;
+        if ((g = track_memory(h, nullptr)) != ROSE_OK) break;
         FitLaunch& L = fit[pos[i]];
         L = FitLaunch{};
         L.g = h->g;

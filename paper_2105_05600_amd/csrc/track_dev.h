@@ -140,12 +140,14 @@ inline UpdateWork* work_of(DevState* st) { return (UpdateWork*)((char*)st + (siz
 
 constexpr size_t kTrackBytes = (sizeof(DevState) + 255) / 256 * 256 + sizeof(UpdateWork);
 
-// a handle's device state and update scratch, allocated on first use
-inline rose_status track_memory(rose_tsdf* h) {
+// A handle's device state and update scratch, allocated on first use and
+// cleared on the stream that first uses it (nullptr: the null stream).  Only
+// that stream is waited for, once.
+inline rose_status track_memory(rose_tsdf* h, hipStream_t s) {
     if (h->st) return ROSE_OK;
     void* p = nullptr;
     ROSE_CHECK_HIP(hipMalloc(&p, kTrackBytes));
-    if (hipMemset(p, 0, kTrackBytes) != hipSuccess || hipDeviceSynchronize() != hipSuccess) {
+    if (hipMemsetAsync(p, 0, kTrackBytes, s) != hipSuccess || hipStreamSynchronize(s) != hipSuccess) {
         (void)hipFree(p);
         set_error("track state: clearing %zu bytes failed", kTrackBytes);
         return ROSE_E_DEVICE;
