@@ -6,6 +6,8 @@
 // (row-vector convention, y = x W + b); gradients and Adam moments use the
 // same layout.  Operands are rounded to BF16 (round to nearest even) as the
 // GEMM tiles are staged in LDS; products accumulate in FP32.
+#include <algorithm>
+
 #include "common.h"
 
 namespace rose {
@@ -33,6 +35,7 @@ struct GemmArgs {
     float* H;          // EPI_BIAS_GELU: GELU(C), same layout as C
     const float* Z;    // EPI_GELU_GRAD: pre-activations, same layout as C
     int32_t mode;
+    int32_t span;  // k that the operands' buffers reach (set by the launch)
 };
 
 // Products: C = A B with binary32 operands rounded to bfloat16 on their way
@@ -55,7 +58,7 @@ __device__ inline int chunk_at(int row, int c) {
 }
 
 // How an operand lies in memory, as rows (m or n) by k.
-enum { LD_K = 0,     // k contiguous: two 16-byte loads per chunk, lanes along k
+enum { LD_K = 0,     // k contiguous (through pointers also backwards): two 16-byte loads per chunk, lanes along k
        LD_ROW = 1 }; // any other strides: 8 loads per chunk, lanes along the rows
 
 struct OpView {
@@ -73,11 +76,13 @@ __device__ inline void load_chunk(const OpView& o, int r, int k, float (&v)[8]) 
     if (r < o.rows && k + 8 <= o.K) {
         const float* q = o.p + r * o.srow + k * o.sk;
         if constexpr (LD == LD_K) {
-            const f32x4_t a = *(const f32x4u_t*)q, b = *(const f32x4u_t*)(q + 4);
+            const bool back = o.sk < 0;
+            const float* first = back ? q - 7 : q;
+            const f32x4_t a = *(const f32x4u_t*)first, b = *(const f32x4u_t*)(first + 4);
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                v[e] = a[e];
-                v[4 + e] = b[e];
+                v[e] = back ? b[3 - e] : a[e];
+                v[4 + e] = back ? a[3 - e] : b[e];
             }
         } else {
 #pragma unroll
@@ -93,11 +98,15 @@ __device__ inline void load_chunk(const OpView& o, int r, int k, float (&v)[8]) 
 // 32-bit offset per chunk, held for the whole product, plus a wave-uniform
 // offset of the k-step.  kNoRow marks a chunk past the last row: at or past
 // the buffer's size with every k-step added, it reads 0.  The launch keeps
-// every offset of a tile (rows and k together) below kNoRow.
+// every offset of a tile (rows and `span` k together) below kNoRow; where that
+// is not all of K (FAR), the buffers' start moves on every `span` k.  That is
+// a kernel of its own: the moving start costs the others 5 % (2048^3: 61 us
+// against 58).
 constexpr uint32_t kNoRow = 0x80000000u;
 
-__device__ inline __amdgpu_buffer_rsrc_t tile_buffer(const OpView& o, int row0) {
-    return __builtin_amdgcn_make_buffer_rsrc((void*)(o.p + row0 * o.srow), (short)0, (int)kNoRow, 0x00020000);
+__device__ inline __amdgpu_buffer_rsrc_t tile_buffer(const OpView& o, int row0, int k0) {
+    return __builtin_amdgcn_make_buffer_rsrc((void*)(o.p + (row0 * o.srow + k0 * o.sk)), (short)0, (int)kNoRow,
+                                             0x00020000);
 }
 
 template <int LD>
@@ -164,7 +173,7 @@ __device__ inline void epilogue(const GemmArgs& g, const f32x16_t& acc, int mt, 
 // instructions and written to the other LDS buffer after them (one barrier
 // per step).  4096^3 with 256 x 256: 0.219 ms, 627 TFLOP/s (1.74 ms, 79
 // TFLOP/s, with one 64 x 64 tile, 4-byte loads and no load ahead).
-template <int BM, int BN, int WM, int WN, int LA, int LB>
+template <int BM, int BN, int WM, int WN, int LA, int LB, bool FAR>
 __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64) void k_gemm_tile(GemmArgs g) {
     constexpr int kThreads = (BM / WM) * (BN / WN) * 64, KC = 32, TM = WM / 32, TN = WN / 32;
     constexpr int CA = BM * (KC / 8) / kThreads, CB = BN * (KC / 8) / kThreads;  // chunks per thread
@@ -192,7 +201,6 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64) void k_gemm_tile(GemmAr
 #pragma unroll
             for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.0f;
     float va[CA][8], vb[CB][8];
-    const __amdgpu_buffer_rsrc_t ra = tile_buffer(A, m0), rb = tile_buffer(B, n0);
     const uint32_t ska = 4u * (uint32_t)g.sak, skb = 4u * (uint32_t)g.sbk;
     uint32_t oa[CA], ob[CB];
 #pragma unroll
@@ -205,22 +213,29 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64) void k_gemm_tile(GemmAr
         const int e = tid + q * kThreads, r = LB == LD_ROW ? e % BN : e / 4, c = LB == LD_ROW ? e / BN : e % 4;
         ob[q] = n0 + r < g.N ? 4u * (uint32_t)g.sbn * r + 8u * skb * c : kNoRow;
     }
+    __amdgpu_buffer_rsrc_t ra = tile_buffer(A, m0, 0), rb = tile_buffer(B, n0, 0);
+    int kbase = 0;  // the buffers' k
     auto fetch = [&](int k0) {
+        if (FAR && k0 - kbase >= g.span) {
+            ra = tile_buffer(A, m0, kbase = k0);
+            rb = tile_buffer(B, n0, kbase);
+        }
+        const int kr = FAR ? k0 - kbase : k0;
         if (k0 + KC <= g.K) {
 #pragma unroll
-            for (int q = 0; q < CA; ++q) load_chunk<LA>(ra, oa[q], k0 * ska, ska, va[q]);
+            for (int q = 0; q < CA; ++q) load_chunk<LA>(ra, oa[q], kr * ska, ska, va[q]);
 #pragma unroll
-            for (int q = 0; q < CB; ++q) load_chunk<LB>(rb, ob[q], k0 * skb, skb, vb[q]);
+            for (int q = 0; q < CB; ++q) load_chunk<LB>(rb, ob[q], kr * skb, skb, vb[q]);
         } else {  // the last, partial step
 #pragma unroll
             for (int q = 0; q < CA; ++q) {
                 const int e = tid + q * kThreads, c = LA == LD_ROW ? e / BM : e % 4;
-                load_chunk_tail(ra, oa[q], k0 * ska, ska, g.K - k0 - 8 * c, va[q]);
+                load_chunk_tail(ra, oa[q], kr * ska, ska, g.K - k0 - 8 * c, va[q]);
             }
 #pragma unroll
             for (int q = 0; q < CB; ++q) {
                 const int e = tid + q * kThreads, c = LB == LD_ROW ? e / BN : e % 4;
-                load_chunk_tail(rb, ob[q], k0 * skb, skb, g.K - k0 - 8 * c, vb[q]);
+                load_chunk_tail(rb, ob[q], kr * skb, skb, g.K - k0 - 8 * c, vb[q]);
             }
         }
     };
@@ -275,7 +290,7 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64) void k_gemm_tile(GemmAr
 // BUF: through the raw buffers of the tile kernels (a 32-bit offset per chunk);
 // otherwise (strides past their range) through plain pointers.
 constexpr int kSmallK = 256;
-template <int LA, int LB, bool BUF>
+template <int LA, int LB, bool BUF, bool FAR>
 __global__ __launch_bounds__(512) void k_gemm_small(GemmArgs g) {
     constexpr int KC = kSmallK, CH = 32 * (KC / 8) / 512;  // chunks per thread and operand
     __shared__ bf16x8_t As[2][32 * (KC / 8)];
@@ -292,7 +307,6 @@ __global__ __launch_bounds__(512) void k_gemm_small(GemmArgs g) {
         *r = ld == LD_ROW ? e % 32 : e / (KC / 8);
         *c = ld == LD_ROW ? e / 32 : e % (KC / 8);
     };
-    const __amdgpu_buffer_rsrc_t ra = tile_buffer(A, m0), rb = tile_buffer(B, n0);
     const uint32_t ska = 4u * (uint32_t)g.sak, skb = 4u * (uint32_t)g.sbk;
     uint32_t oa[CH], ob[CH];
 #pragma unroll
@@ -303,23 +317,30 @@ __global__ __launch_bounds__(512) void k_gemm_small(GemmArgs g) {
         at(LB, q, &r, &c);
         ob[q] = n0 + r < g.N ? 4u * (uint32_t)g.sbn * r + 8u * skb * c : kNoRow;
     }
+    __amdgpu_buffer_rsrc_t ra = tile_buffer(A, m0, 0), rb = tile_buffer(B, n0, 0);
+    int kbase = 0;  // the buffers' k
     auto fetch = [&](int k0, float (&va)[CH][8], float (&vb)[CH][8]) {
         const bool full = k0 + KC <= g.K;
+        if (FAR && k0 - kbase >= g.span) {
+            ra = tile_buffer(A, m0, kbase = k0);
+            rb = tile_buffer(B, n0, kbase);
+        }
+        const int kr = FAR ? k0 - kbase : k0;
 #pragma unroll
         for (int q = 0; q < CH; ++q) {
             int r, c;
             at(LA, q, &r, &c);
             if constexpr (!BUF) load_chunk<LA>(A, m0 + r, k0 + 8 * c, va[q]);
-            else if (full) load_chunk<LA>(ra, oa[q], k0 * ska, ska, va[q]);
-            else load_chunk_tail(ra, oa[q], k0 * ska, ska, g.K - k0 - 8 * c, va[q]);
+            else if (full) load_chunk<LA>(ra, oa[q], kr * ska, ska, va[q]);
+            else load_chunk_tail(ra, oa[q], kr * ska, ska, g.K - k0 - 8 * c, va[q]);
         }
 #pragma unroll
         for (int q = 0; q < CH; ++q) {
             int r, c;
             at(LB, q, &r, &c);
             if constexpr (!BUF) load_chunk<LB>(B, n0 + r, k0 + 8 * c, vb[q]);
-            else if (full) load_chunk<LB>(rb, ob[q], k0 * skb, skb, vb[q]);
-            else load_chunk_tail(rb, ob[q], k0 * skb, skb, g.K - k0 - 8 * c, vb[q]);
+            else if (full) load_chunk<LB>(rb, ob[q], kr * skb, skb, vb[q]);
+            else load_chunk_tail(rb, ob[q], kr * skb, skb, g.K - k0 - 8 * c, vb[q]);
         }
     };
     fetch(0, va[0], vb[0]);
@@ -445,11 +466,16 @@ __global__ __launch_bounds__(256) void k_adam(int64_t n, float* p, const float* 
     p[i] = p[i] - lr * (mi / c1) / (sqrtf(vi / c2) + eps);
 }
 
-// whether every offset of a 256-row tile of an operand, over all k, fits the
-// tile kernels' 32-bit buffer offsets
-static bool tile_fits(int64_t srow, int64_t sk, int32_t K) {
-    if (srow < 0 || sk < 0 || srow >= (1 << 21) || sk >= (1 << 29)) return false;
-    return 4 * (256 * srow + (int64_t)(K + 32) * sk) < (int64_t)kNoRow;
+// How many k (a multiple of a kernel's k-step ks, or all K) the offsets of an
+// operand's tile of `rows` rows reach with 31 bits, a step and a chunk past
+// the last k included; 0: not even one step.
+static int32_t tile_span(int64_t srow, int64_t sk, int32_t rows, int32_t ks, int32_t K) {
+    if (srow < 0 || sk < 0 || srow >= (1 << 29) || sk >= (1 << 29)) return 0;
+    const int64_t left = ((int64_t)kNoRow - 1) / 4 - rows * srow;
+    const int32_t past = std::min(ks, K) + 8;
+    if (left < past * sk) return 0;
+    const int64_t k = sk > 0 ? left / sk - past : K;
+    return k >= K ? K : (int32_t)(k / ks * ks);
 }
 
 // Kernel by output size and K (rows and columns contiguous in memory, us):
@@ -463,26 +489,40 @@ static bool tile_fits(int64_t srow, int64_t sk, int32_t K) {
 // so a wider tile is taken once it leaves (almost) every CU a workgroup --
 // two of them with 128 x 128, whose waves alone do not hide their loads.
 template <int LA, int LB>
-static void launch_gemm(const GemmArgs& g, hipStream_t s) {
+static void launch_gemm(GemmArgs g, hipStream_t s) {
     auto tiles = [&](int t) { return (int64_t)((g.M + t - 1) / t) * ((g.N + t - 1) / t); };
-    const bool fits = tile_fits(g.sam, g.sak, g.K) && tile_fits(g.sbn, g.sbk, g.K);
-    if (fits && g.K >= 512 && tiles(256) >= 192)
-        hipLaunchKernelGGL((k_gemm_tile<256, 256, 128, 64, LA, LB>), dim3((unsigned)tiles(256)), dim3(512), 0, s, g);
-    else if (fits && g.K >= 512 && tiles(128) >= 256)
-        hipLaunchKernelGGL((k_gemm_tile<128, 128, 64, 64, LA, LB>), dim3((unsigned)tiles(128)), dim3(256), 0, s, g);
-    else if (fits && tiles(64) >= 192)
-        hipLaunchKernelGGL((k_gemm_tile<64, 64, 32, 32, LA, LB>), dim3((unsigned)tiles(64)), dim3(256), 0, s, g);
-    else if (fits)
-        hipLaunchKernelGGL((k_gemm_small<LA, LB, true>), dim3((g.N + 31) / 32, (g.M + 31) / 32), dim3(512), 0, s, g);
-    else
-        hipLaunchKernelGGL((k_gemm_small<LD_ROW, LD_ROW, false>), dim3((g.N + 31) / 32, (g.M + 31) / 32), dim3(512),
-                           0, s, g);
+    auto reach = [&](int rows, int ks) {
+        g.span = std::min(tile_span(g.sam, g.sak, std::min(rows, g.M), ks, g.K),
+                          tile_span(g.sbn, g.sbk, std::min(rows, g.N), ks, g.K));
+        return g.span > 0;
+    };
+    auto go = [&](auto near, auto far, dim3 blocks, int threads) {
+        hipLaunchKernelGGL(g.span < g.K ? far : near, blocks, dim3(threads), 0, s, g);
+    };
+    const dim3 small((g.N + 31) / 32, (g.M + 31) / 32);
+    if (g.K >= 512 && tiles(256) >= 192 && reach(256, 32))
+        go(&k_gemm_tile<256, 256, 128, 64, LA, LB, false>, &k_gemm_tile<256, 256, 128, 64, LA, LB, true>,
+           dim3((unsigned)tiles(256)), 512);
+    else if (g.K >= 512 && tiles(128) >= 256 && reach(128, 32))
+        go(&k_gemm_tile<128, 128, 64, 64, LA, LB, false>, &k_gemm_tile<128, 128, 64, 64, LA, LB, true>,
+           dim3((unsigned)tiles(128)), 256);
+    else if (tiles(64) >= 192 && reach(64, 32))
+        go(&k_gemm_tile<64, 64, 32, 32, LA, LB, false>, &k_gemm_tile<64, 64, 32, 32, LA, LB, true>,
+           dim3((unsigned)tiles(64)), 256);
+    else if (reach(32, kSmallK))
+        go(&k_gemm_small<LA, LB, true, false>, &k_gemm_small<LA, LB, true, true>, small, 512);
+    else {  // row pitches of 64 MB or more, and negative strides
+        const bool ka = g.sak == 1 || g.sak == -1, kb = g.sbk == 1 || g.sbk == -1;
+        auto plain = kb ? (ka ? &k_gemm_small<LD_K, LD_K, false, false> : &k_gemm_small<LD_ROW, LD_K, false, false>)
+                        : (ka ? &k_gemm_small<LD_K, LD_ROW, false, false> : &k_gemm_small<LD_ROW, LD_ROW, false, false>);
+        hipLaunchKernelGGL(plain, small, dim3(512), 0, s, g);
+    }
 }
 
 static rose_status gemm(int M, int N, int K, const float* A, int64_t sam, int64_t sak, const float* B, int64_t sbk,
                         int64_t sbn, float* C, int64_t ldc, int mode, const float* bias, float* H, const float* Z,
                         hipStream_t s) {
-    GemmArgs g{M, N, K, A, sam, sak, B, sbk, sbn, C, ldc, bias, H, Z, mode};
+    GemmArgs g{M, N, K, A, sam, sak, B, sbk, sbn, C, ldc, bias, H, Z, mode, K};
     if (sak == 1) sbk == 1 ? launch_gemm<LD_K, LD_K>(g, s) : launch_gemm<LD_K, LD_ROW>(g, s);
     else sbk == 1 ? launch_gemm<LD_ROW, LD_K>(g, s) : launch_gemm<LD_ROW, LD_ROW>(g, s);
     ROSE_CHECK_HIP(hipGetLastError());
