@@ -37,6 +37,7 @@ struct RaycastArgs {
     int32_t W, H;
     double fx, fy, cx, cy;
     double near_z, far_z, step;
+    double inv_vox, kmax;  // 1 / vox; (far - near) / step + 2
     float* out;
 };
 
@@ -49,25 +50,28 @@ __device__ inline double ray_sample(const RaycastArgs& a, const double dw[3], do
     return trilinear64<FMT>(a.g, h[0], h[1], h[2]);
 }
 
-// Whether a sample of a ray may be <= 0: no, when it is outside the grid (+1)
-// or all 8 corners are > 0 (the interpolation weights are >= 0 and not all
-// 0); yes (the sample is then evaluated), when a corner is <= 0 or NaN, or
-// its voxel coordinates are so close to a voxel or grid boundary that the
-// corners are not certain.  The coordinates are i0 + f with the voxel i0 of a
-// stretch's first sample and f = f0 + d b in binary32 (d below 128, |b| at
-// most 8 voxels: within 1e-4 of ray_sample's).  Loads are unconditional
-// (voxel 0 for the lanes that do not need theirs), so that those of several
-// samples are in flight together.
+// What a sample of a ray can be.  Outside the grid it is +1; inside it is <= 0
+// only if a corner is, and > 0 only if a corner is (the interpolation weights
+// are >= 0 and not all 0; with a NaN corner it is NaN).  Where its
+// voxel coordinates are so close to a voxel or grid boundary that the corners
+// are not certain, it can be anything.  The coordinates are i0 + f with the
+// voxel i0 of a stretch's first sample and f = f0 + d b in binary32 (d below
+// 128, |b| at most 8 voxels: within 1e-4 of ray_sample's).  Loads are
+// unconditional (voxel 0 for the lanes that do not need theirs), so that
+// those of several samples are in flight together.
 struct RayTest {
-    float v[8];
+    int v[8];  // the corners' signs: > 0 or <= 0 as the value (a NaN's by its sign bit)
     bool outside, unsure;
 };
 
-// sign-exact value of a 16-bit voxel
+// sign of a voxel from its bits
+__device__ inline int sign_of(uint32_t bits) { return (int)bits; }
+__device__ inline int sign_of(unsigned short bits) { return (int16_t)bits; }
+
 template <int FMT>
-__device__ inline float psi_of_bits(unsigned short b) {
-    if constexpr (FMT == ROSE_TSDF_F16) return __half2float(__ushort_as_half(b));
-    else return (float)(int16_t)b;
+__device__ inline int load_sign(const void* psi, uint32_t off) {
+    if constexpr (FMT == ROSE_TSDF_F32) return sign_of(((const uint32_t*)psi)[off]);
+    else return sign_of(((const unsigned short*)psi)[off]);
 }
 
 template <int FMT, bool WIDE>
@@ -94,7 +98,7 @@ __device__ inline void ray_test_load(const Grid& g, __amdgpu_buffer_rsrc_t psi, 
                            __umul24((i[2] + 1) & ~7u, (uint32_t)g.bstride_z) + 64 * (i[2] + 1)};
     if constexpr (WIDE) {
 #pragma unroll
-        for (int e = 0; e < 8; ++e) t.v[e] = load_psi<FMT>(g.psi, x[e & 1] + y[(e >> 1) & 1] + z[e >> 2]);
+        for (int e = 0; e < 8; ++e) t.v[e] = load_sign<FMT>(g.psi, x[e & 1] + y[(e >> 1) & 1] + z[e >> 2]);
         return;
     }
     // the two x neighbours of a corner row in one load, except across a brick
@@ -106,13 +110,13 @@ __device__ inline void ray_test_load(const Grid& g, __amdgpu_buffer_rsrc_t psi, 
         const uint32_t off = x[0] + y[e & 1] + z[e >> 1];
         if constexpr (FMT == ROSE_TSDF_F32) {
             const auto w = __builtin_amdgcn_raw_buffer_load_b64(psi, (int)(4u * off), 0, 0);
-            t.v[2 * e] = __uint_as_float(w[0]);
-            t.v[2 * e + 1] = __uint_as_float(w[1]);
+            t.v[2 * e] = sign_of(w[0]);
+            t.v[2 * e + 1] = sign_of(w[1]);
         } else {  // the 4 values from the 4-byte boundary at or below
             const auto w = __builtin_amdgcn_raw_buffer_load_b64(psi, (int)(2u * (off & ~1u)), 0, 0);
             const uint32_t pair = __builtin_amdgcn_alignbit(w[1], w[0], 16u * (off & 1u));
-            t.v[2 * e] = psi_of_bits<FMT>((unsigned short)pair);
-            t.v[2 * e + 1] = psi_of_bits<FMT>((unsigned short)(pair >> 16));
+            t.v[2 * e] = sign_of((unsigned short)pair);
+            t.v[2 * e + 1] = sign_of((unsigned short)(pair >> 16));
         }
     }
     if (split) {
@@ -120,18 +124,20 @@ __device__ inline void ray_test_load(const Grid& g, __amdgpu_buffer_rsrc_t psi, 
         for (int e = 0; e < 4; ++e) {
             const uint32_t off = x[1] + y[e & 1] + z[e >> 1];
             if constexpr (FMT == ROSE_TSDF_F32)
-                t.v[2 * e + 1] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(psi, (int)(4u * off), 0, 0));
+                t.v[2 * e + 1] = sign_of((uint32_t)__builtin_amdgcn_raw_buffer_load_b32(psi, (int)(4u * off), 0, 0));
             else
-                t.v[2 * e + 1] = psi_of_bits<FMT>(__builtin_amdgcn_raw_buffer_load_b16(psi, (int)(2u * off), 0, 0));
+                t.v[2 * e + 1] = sign_of((unsigned short)__builtin_amdgcn_raw_buffer_load_b16(psi, (int)(2u * off), 0, 0));
         }
     }
 }
 
-__device__ inline bool ray_test(const RayTest& t) {
-    bool pos = true;
+// whether the sample may be > 0 (POS) or <= 0
+template <bool POS>
+__device__ inline bool ray_may_be(const RayTest& t) {
+    int m = t.v[0];
 #pragma unroll
-    for (int e = 0; e < 8; ++e) pos = pos && t.v[e] > 0.0f;
-    return t.unsure || (!t.outside && !pos);
+    for (int e = 1; e < 8; ++e) m = POS ? max(m, t.v[e]) : min(m, t.v[e]);
+    return t.unsure || (!t.outside && (POS ? m > 0 : m <= 0));
 }
 
 // The fixed-step march of the rays: a wavefront takes a TP x TP patch of
@@ -139,12 +145,13 @@ __device__ inline bool ray_test(const RayTest& t) {
 // the same expression as a serial march, so the samples are identical), U
 // such groups in flight together.  A crossing at k is a + to - change
 // between samples k-1 and k inside the truncation band, so only a sample
-// that may be <= 0 and the one before it need a value: the others (free
-// space, the bulk of every ray) are told by ray_test.  The first crossing in
-// step order gives the depth by linear interpolation, exactly as a serial
-// march stopping there would.  Bound by the gathers' cache-line lookups (8
-// corners per sample in 4 loads; with one load per corner 258 us at 320 x
-// 240, whatever the arithmetic around them).
+// that may be <= 0 after one that may be > 0 needs a value, and that one
+// with it: ray_may_be tells the others (free space, and the inside of solids,
+// the bulk of every ray).  The first crossing in step order gives the depth
+// by linear interpolation, exactly as a serial march stopping there would.
+// Bound by the gathers' cache-line lookups (8 corners per sample in 4 loads;
+// with one load per corner 258 us at 320 x 240, whatever the arithmetic
+// around them).
 template <int FMT, bool WIDE, int TP, int U>
 __global__ __launch_bounds__(256) void k_raycast(RaycastArgs a) {
     constexpr int NS = kWave / (TP * TP);
@@ -159,11 +166,11 @@ __global__ __launch_bounds__(256) void k_raycast(RaycastArgs a) {
     const uint32_t bytes = (uint32_t)a.g.nx * (uint32_t)a.g.ny * (uint32_t)a.g.nz * (FMT == ROSE_TSDF_F32 ? 4u : 2u);
     const __amdgpu_buffer_rsrc_t psi = __builtin_amdgcn_make_buffer_rsrc(a.g.psi, (short)0, (int)bytes, 0x00020000);
     // voxel coordinates ha + k hb; where they are too large or too far apart
-    // for ray_test's margin, every sample is evaluated
+    // for RayTest's margin, every sample is evaluated
     double ha[3], hb[3];
     float fb[3];
     bool plain = false;
-    const double inv = 1.0 / (double)a.g.vox, kmax = (a.far_z - a.near_z) / a.step + 2.0;
+    const double inv = a.inv_vox, kmax = a.kmax;
     for (int c = 0; c < 3; ++c) {
         ha[c] = (a.t[c] + a.near_z * dw[c] - (double)a.g.origin[c]) * inv - 0.5;
         hb[c] = a.step * dw[c] * inv;
@@ -172,11 +179,14 @@ __global__ __launch_bounds__(256) void k_raycast(RaycastArgs a) {
                                fabs(a.near_z * dw[c]) * inv < 1e8) || !(fabs(hb[c]) <= 8.0);
     }
     // samples before the ray enters the grid and after it leaves it are +1
+    // (the reciprocal's rounding is far below the margins of 1e-3 voxels and
+    // 2 samples)
     double k0 = 0.0, k1 = kmax;
     if (!plain) {
         const int32_t n[3] = {a.g.nx, a.g.ny, a.g.nz};
         for (int c = 0; c < 3; ++c) {
-            const double e0 = (-1e-3 - ha[c]) / hb[c], e1 = ((double)(n[c] - 1) + 1e-3 - ha[c]) / hb[c];
+            const double ib = 1.0 / hb[c];
+            const double e0 = (-1e-3 - ha[c]) * ib, e1 = ((double)(n[c] - 1) + 1e-3 - ha[c]) * ib;
             if (hb[c] > 0.0) {
                 k0 = fmax(k0, e0);
                 k1 = fmin(k1, e1);
@@ -190,6 +200,9 @@ __global__ __launch_bounds__(256) void k_raycast(RaycastArgs a) {
     int base = (int)fmin(fmax(k0 - 2.0, 0.0), kmax);
     double out = 0.0;
     bool done = u >= a.W || v >= a.H || base > kend;
+    // lanes that hold a pixel's first sample of a group
+    constexpr uint64_t kFirst = NS == 64 ? 1ull : NS == 16 ? 0x0001000100010001ull : 0x1111111111111111ull;
+    uint64_t carry = kFirst;  // of these, the ones whose sample before may be > 0
     for (; !done; base += U * NS, done = done || base > kend) {
         int i0[3];
         float f0[3];
@@ -207,10 +220,17 @@ __global__ __launch_bounds__(256) void k_raycast(RaycastArgs a) {
             if (done) break;
             const int k = base + q * NS + j;
             const double z = a.near_z + (double)k * a.step;
-            const bool valid = !(z > a.far_z);
+            const bool neg = k >= 1 && !(z > a.far_z) && (plain || ray_may_be<false>(t[q]));
+            if (!__ballot(neg)) {  // free space: most groups
+                carry = kFirst;
+                continue;
+            }
+            const uint64_t pos = __ballot(plain || ray_may_be<true>(t[q]));
+            const uint64_t after = ((pos << 1) & ~kFirst) | carry;
+            carry = (pos >> (NS - 1)) & kFirst;
             double prev = 0.0, s = 1.0;
             bool cross = false;
-            if (valid && k >= 1 && (plain || ray_test(t[q]))) {
+            if (neg && __builtin_amdgcn_inverse_ballot_w64(after)) {
                 s = ray_sample<FMT>(a, dw, z);
                 if (s <= 0.0 && s > -1.0) {
                     prev = ray_sample<FMT>(a, dw, a.near_z + (double)(k - 1) * a.step);
@@ -307,6 +327,8 @@ rose_status tsdf_raycast(const rose_tsdf* h, const rose_pose* T_wc, const rose_c
     a.H = cam->height;
     a.fx = cam->fx; a.fy = cam->fy; a.cx = cam->cx; a.cy = cam->cy;
     a.near_z = near_m; a.far_z = far_m; a.step = step_m;
+    a.inv_vox = 1.0 / (double)h->g.vox;
+    a.kmax = (far_m - near_m) / step_m + 2.0;
     a.out = depth_out_dev;
     if (h->g.fmt == ROSE_TSDF_F32) launch_raycast_fmt<ROSE_TSDF_F32>(a, s);
     else if (h->g.fmt == ROSE_TSDF_F16) launch_raycast_fmt<ROSE_TSDF_F16>(a, s);

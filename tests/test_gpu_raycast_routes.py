@@ -1,0 +1,76 @@
+"""tsdf_raycast through each of its kernels (by image size) where samples of a ray can be anything: a camera inside a solid of -1,
+in free space, and in a volume of random signs with NaN; steps that are a
+small part of a voxel and steps of many voxels.  Bit for bit against the
+oracle's serial march."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+DIMS, VOX, ORG = (40, 48, 32), 0.03, (0.3, -0.2, 0.1)
+
+
+def _volume(kind, rng):
+    nx, ny, nz = DIMS
+    z, y, x = np.meshgrid(np.arange(nz), np.arange(ny), np.arange(nx), indexing="ij")
+    if kind == "signs":  # + and - cells next to one another, some NaN
+        psi = rng.uniform(-1.2, 1.2, (nz, ny, nx)).clip(-1, 1).astype(np.float32)
+        psi[rng.random(psi.shape) < 0.01] = np.float32("nan")
+        return psi
+    d = np.sqrt((x - nx * 0.5) ** 2 + (y - ny * 0.5) ** 2 + (z - nz * 0.5) ** 2)
+    shell = 1.0 - np.abs(d - 12.0) / 3.0  # a shell of free space 3 voxels thick, solid inside and outside
+    return (np.where(shell > 0, 1.0, -1.0) if kind == "solid" else np.clip(14.0 - d, -1, 1)).astype(np.float32)
+
+
+# 1, 4 and 16 pixels per wavefront
+@pytest.mark.parametrize("w,h,step_vox", [(23, 17, 0.5), (61, 53, 0.04), (131, 119, 0.3), (131, 119, 9.0),
+                                          (180, 170, 9.0), (521, 510, 0.5), (521, 510, 9.0)])
+@pytest.mark.parametrize("kind", ["solid", "free", "signs"])
+@pytest.mark.parametrize("fmt", [0, 1, 2])
+def test_routes(orc, kind, fmt, w, h, step_vox):
+    from paper_2105_05600_amd import rose
+
+    class K:
+        width, height, fx, fy, cx, cy = w, h, 0.8 * w, 0.8 * w, w / 2 - 0.5, h / 2 - 0.5
+
+    rng = np.random.default_rng(w + fmt)
+    psi = _volume(kind, rng)
+    if fmt == 2:
+        psi = np.nan_to_num(psi)  # the integer format has no NaN
+    vol = rose.Tsdf(DIMS, VOX, 0.12, ORG, fmt=fmt)
+    vol.load(torch.from_numpy(psi).cuda())
+    psi = vol.export()[0].cpu().numpy()
+    q = rng.standard_normal(4)
+    q /= np.linalg.norm(q)
+    centre = np.array(ORG) + VOX * np.array(DIMS) / 2
+    for t in (centre, centre + VOX * np.array([5.0, -13.0, 2.0])):
+        g = rose.raycast(vol, q, t, K, near=0.02, far=2.2, step=step_vox * VOX).cpu().numpy()
+        o = orc.raycast(psi, VOX, np.array(ORG), q, t, K, near=0.02, far=2.2, step=step_vox * VOX)
+        assert np.array_equal(g, np.asarray(o, np.float32).reshape(g.shape))
+
+
+def test_the_inside_of_a_solid_is_marched_like_free_space():
+    """Rays that stay in a solid of -1 take no more than 1.25 times the time of rays in free space."""
+    from paper_2105_05600_amd import rose
+
+    class K:
+        width, height, fx, fy, cx, cy = 320, 240, 260.0, 260.0, 159.5, 119.5
+
+    t = []
+    for value, z0 in ((1.0, 0.1017), (-1.0, 0.1017)):
+        vol = rose.Tsdf((256, 256, 256), 0.01, 0.05, (0.0, 0.0, 0.0))
+        vol.load(torch.full((256, 256, 256), value, device="cuda"))
+        best = 1e9
+        for _ in range(5):
+            e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            e0.record()
+            for _ in range(20):
+                out = rose.raycast(vol, [1.0, 0, 0, 0], [1.28, 1.28, z0], K, near=0.1, far=4.0, step=0.005)
+            e1.record()
+            e1.synchronize()
+            best = min(best, e0.elapsed_time(e1))
+        assert not bool(out.any())
+        t.append(best)
+        vol.close()
+    assert t[1] < 1.25 * t[0]
