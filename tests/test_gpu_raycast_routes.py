@@ -1,6 +1,6 @@
 """tsdf_raycast through each of its kernels (by image size) where samples of a ray can be anything: a camera inside a solid of -1,
 in free space, and in a volume of random signs with NaN; steps that are a
-small part of a voxel and steps of many voxels.  Bit for bit against the
+small part of a voxel and steps of many voxels; cameras along an axis.  Bit for bit against the
 oracle's serial march."""
 import numpy as np
 import pytest
@@ -44,21 +44,24 @@ def test_routes(orc, kind, fmt, w, h, step_vox):
     q = rng.standard_normal(4)
     q /= np.linalg.norm(q)
     centre = np.array(ORG) + VOX * np.array(DIMS) / 2
-    for t in (centre, centre + VOX * np.array([5.0, -13.0, 2.0])):
+    # the last along an axis, samples on voxel boundaries where the step allows it
+    for q, t in ((q, centre), (q, centre + VOX * np.array([5.0, -13.0, 2.0])),
+                 (np.array([1.0, 0, 0, 0]), np.array(ORG) + VOX * np.array([20.5, 24.5, 2.5]))):
         g = rose.raycast(vol, q, t, K, near=0.02, far=2.2, step=step_vox * VOX).cpu().numpy()
         o = orc.raycast(psi, VOX, np.array(ORG), q, t, K, near=0.02, far=2.2, step=step_vox * VOX)
         assert np.array_equal(g, np.asarray(o, np.float32).reshape(g.shape))
 
 
 def test_the_inside_of_a_solid_is_marched_like_free_space():
-    """Rays that stay in a solid of -1 take no more than 1.25 times the time of rays in free space."""
+    """Rays that stay in a solid of -1, and rays whose samples lie on voxel boundaries (a camera along an axis, at a
+    half-voxel step), take no more than 1.5 times the time of rays in free space."""
     from paper_2105_05600_amd import rose
 
     class K:
         width, height, fx, fy, cx, cy = 320, 240, 260.0, 260.0, 159.5, 119.5
 
     t = []
-    for value, z0 in ((1.0, 0.1017), (-1.0, 0.1017)):
+    for value, z0 in ((1.0, 0.1017), (-1.0, 0.1017), (1.0, 0.1)):
         vol = rose.Tsdf((256, 256, 256), 0.01, 0.05, (0.0, 0.0, 0.0))
         vol.load(torch.full((256, 256, 256), value, device="cuda"))
         best = 1e9
@@ -73,4 +76,4 @@ def test_the_inside_of_a_solid_is_marched_like_free_space():
         assert not bool(out.any())
         t.append(best)
         vol.close()
-    assert t[1] < 1.25 * t[0]
+    assert max(t[1:]) < 1.5 * t[0]
