@@ -1,5 +1,7 @@
 // Inputs of the learned PST proposal: a low-resolution raycast of the TSDF
 // at the previous pose and the depth residual against the current frame.
+#include <algorithm>
+
 #include "common.h"
 
 namespace rose {
@@ -272,17 +274,56 @@ __global__ __launch_bounds__(256) void k_raycast(RaycastArgs a) {
     if (j == 0 && u < a.W && v < a.H) a.out[(int64_t)v * a.W + u] = (float)out;
 }
 
+// Every sample evaluated: a wavefront per pixel, lane j taking sample
+// base + j, the sample before it from the lane below.
+template <int FMT>
+__global__ __launch_bounds__(256) void k_raycast_each(RaycastArgs a) {
+    const int lane = threadIdx.x & 63;
+    const int idx = blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (idx >= a.W * a.H) return;  // whole wavefronts leave together
+    const int u = idx % a.W, v = idx / a.W;
+    const double dc[3] = {((double)u - a.cx) / a.fx, ((double)v - a.cy) / a.fy, 1.0};
+    double dw[3];
+    for (int i = 0; i < 3; ++i) dw[i] = a.R[3 * i + 0] * dc[0] + a.R[3 * i + 1] * dc[1] + a.R[3 * i + 2] * dc[2];
+    double carry = 0.0, out = 0.0;  // sample base - 1 (from the round before)
+    for (int base = 0;; base += kWave) {
+        const int k = base + lane;
+        const double z = a.near_z + (double)k * a.step;
+        const bool valid = !(z > a.far_z);
+        const double s = valid ? ray_sample<FMT>(a, dw, z) : 0.0;
+        double prev = __shfl_up(s, 1, kWave);
+        if (lane == 0) prev = carry;
+        const uint64_t hits = __ballot(valid && k >= 1 && prev > 0.0 && s <= 0.0 && prev < 1.0 && s > -1.0);
+        if (hits) {
+            const double o = a.near_z + (double)(k - 1) * a.step + a.step * prev / (prev - s);
+            out = __shfl(o, __ffsll((unsigned long long)hits) - 1, kWave);
+            break;
+        }
+        if (__ballot(!valid)) break;  // past `far`: so are all later samples
+        carry = __shfl(s, kWave - 1, kWave);
+    }
+    if (lane == 0) a.out[idx] = (float)out;
+}
+
 template <int FMT, bool WIDE>
 static void launch_raycast(const RaycastArgs& a, hipStream_t s) {
     auto blocks = [&](int tp) { return dim3((unsigned)((((a.W + tp - 1) / tp) * ((a.H + tp - 1) / tp) + 3) / 4)); };
     // A patch of neighbouring rays shares lines that the samples along one ray
-    // do not, but leaves fewer wavefronts, whose rounds follow one another
-    // (512^3 at 1 cm, half-voxel steps, us with 1 / 4 / 16 pixels per
-    // wavefront): 80 x 60 19 / 33 / 110, 160 x 120 56 / 50 / 114, 320 x 240
-    // 190 / 139 / 151, 640 x 480 728 / 481 / 436; 239 and 904 us at the last
-    // two sizes with every sample evaluated.
+    // do not, but leaves fewer wavefronts, whose rounds follow one another;
+    // with few samples per ray in a small image the rounds are few and each
+    // one's setup and dependent loads count.  384 x 392 x 248, a room, us with
+    // every sample evaluated / 1 / 4 / 16 pixels per wavefront:
+    //   40 x 30, 1200 samples per ray 11 / 11 / 25 / 93
+    //   120 x 90, 1200: 31 / 28 / 34 / 85, 400: 19 / 23 / 18 / 37
+    //   160 x 120, 1200: 51 / 45 / 38 / 86, 200: 18 / 30 / 17 / 23, 55: 12 / 22 / 17 / 16
+    //   320 x 240, 1200: 186 / - / 112 / 117, 55: 43 / - / 39 / 26
+    //   640 x 480, 1200: 733 / - / - / 336, 55: 165 / - / - / 95
     const int64_t pixels = (int64_t)a.W * a.H;
-    if (pixels < 15000) hipLaunchKernelGGL((k_raycast<FMT, WIDE, 1, 2>), blocks(1), dim3(256), 0, s, a);
+    const double nx = a.g.nx, ny = a.g.ny, nz = a.g.nz;
+    const double samples = std::min(a.kmax, sqrt(nx * nx + ny * ny + nz * nz) * (double)a.g.vox / a.step);
+    if (pixels < 3000 || samples < (pixels < 15000 ? 1000.0 : pixels < 30000 ? 128.0 : 0.0))
+        hipLaunchKernelGGL((k_raycast_each<FMT>), blocks(1), dim3(256), 0, s, a);
+    else if (pixels < 15000) hipLaunchKernelGGL((k_raycast<FMT, WIDE, 1, 2>), blocks(1), dim3(256), 0, s, a);
     else if (pixels < (1 << 18)) hipLaunchKernelGGL((k_raycast<FMT, WIDE, 2, 2>), blocks(2), dim3(256), 0, s, a);
     else hipLaunchKernelGGL((k_raycast<FMT, WIDE, 4, 2>), blocks(4), dim3(256), 0, s, a);
 }
