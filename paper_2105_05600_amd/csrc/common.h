@@ -419,7 +419,7 @@ namespace rose {
 struct FitLaunch {
     Grid g;
     const float4* pts;
-    const int32_t* count_dev;  // device point count, or nullptr to use `count`
+    const int32_t* count_dev;  // device point count (at most `count`), or nullptr to use `count`
     int32_t count;
     const float* T32;
     const DevState* st;
@@ -435,7 +435,7 @@ struct FitLaunch {
     int32_t pl_side;
     float pl_thr;   // voxels
     float pl_zref;  // metres: depth at which a rotation axis length is turned into a displacement
-    int32_t ones_lds;          // 1: points-across workgroups stage the brick bits in LDS (set by the launch)
+    int32_t ones_burst;        // 1: the brick bits are staged with all loads in flight (set by the launch)
     uint64_t* partial;         // n x splits x kPartSub grid integers (partial_index)
 };
 

@@ -75,6 +75,34 @@ __host__ __device__ inline uint32_t ones_words(const Grid& g) {
     return ((uint32_t)g.nbx * (uint32_t)g.nby * (uint32_t)g.nbz + 31u) / 32u;
 }
 
+// How a points-across kernel reads the brick bits: from memory, from LDS, or
+// as each sequence's volume allows (the persistent kernel)
+enum { BITS_MEMORY = 0, BITS_LDS = 1, BITS_EITHER = 2 };
+
+// Copies the brick bits to LDS: a word per thread and round, or (burst) 16
+// bytes per lane and load with all loads of a thread in flight before its
+// first write.  LDS has room for a whole number of these (ones_lds_bytes);
+// past the bits the buffer gives 0.
+template <int THREADS>
+__device__ inline void stage_ones(const Grid& g, uint32_t words, uint32_t* s_ones, bool burst) {
+    if (!burst) {
+        for (uint32_t w = threadIdx.x; w < words; w += THREADS) s_ones[w] = g.ones[w];
+        return;
+    }
+    typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
+    constexpr int kLoads = kOnesLdsWords / 4 / THREADS;
+    const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(g.ones, (short)0, (int)(4u * words), 0x00020000);
+    u32x4_t v[kLoads];
+#pragma unroll
+    for (int q = 0; q < kLoads; ++q)
+        v[q] = __builtin_amdgcn_raw_buffer_load_b128(r, 16 * ((int)threadIdx.x + q * THREADS), 0, 0);
+#pragma unroll
+    for (int q = 0; q < kLoads; ++q) {
+        const uint32_t i = threadIdx.x + q * THREADS;
+        if (4 * i < words) ((u32x4_t*)s_ones)[i] = v[q];
+    }
+}
+
 template <int FMT, bool WIDE>
 __device__ inline float gather(const Grid& g, const PsiBuf& b, uint32_t off) {
     if constexpr (WIDE) {
@@ -300,10 +328,10 @@ __device__ inline void add_sq(uint64_t& acc, float& accf, float v) {
 // a binary32 sum (no-Kahan ablation) as a grid integer
 __device__ inline uint64_t grid_of_f32_sum(float f) { return (uint64_t)__double2ull_rn((double)f * 0x1p39); }
 
-// s_ones: LDS for the brick bits (staged here when they fit; `staged` tells
-// whether the previous item of a persistent workgroup left them there), or
-// nullptr.  Every exit before the barrier is uniform over the workgroup.
-template <int P, int U, int FMT, int LK, bool FROM_STATE, bool WIDE, bool ACC32 = false, int WG = 4>
+// s_ones: LDS for the brick bits (staged here, when they fit if BITS_EITHER;
+// `staged` tells whether the previous item of a persistent workgroup left them
+// there).  Every exit before the barrier is uniform over the workgroup.
+template <int P, int U, int FMT, int LK, bool FROM_STATE, bool WIDE, bool ACC32, int WG, int BITS>
 __device__ void fitness_body(const FitLaunch& a, const int blk, uint32_t* s_ones, bool staged = false) {
     constexpr int kU = U;
     constexpr int kStep = kWave * kU;
@@ -324,12 +352,13 @@ __device__ void fitness_body(const FitLaunch& a, const int blk, uint32_t* s_ones
     const int p0 = group * P;
     if (FROM_STATE && (a.st->stopped || switch_skips(a))) return;
     // Evaluations outside the grid or in a brick that holds only +1 are
-    // counted (see nout below); kLds: the brick bits are read from LDS
+    // counted (see nout below); lds: the brick bits are read from LDS
     constexpr bool kCount = (LK == ROSE_LOOKUP_NEAREST) && !ACC32 && !WIDE;
+    static_assert(kCount || BITS == BITS_MEMORY, "brick bits are not read");
     const uint32_t words = ones_words(a.g);
-    const bool lds = kCount && s_ones != nullptr && words <= kOnesLdsWords;
+    const bool lds = BITS == BITS_LDS || (BITS == BITS_EITHER && s_ones != nullptr && words <= kOnesLdsWords);
     if (lds && !staged) {
-        for (uint32_t w = threadIdx.x; w < words; w += kWave * WG) s_ones[w] = a.g.ones[w];
+        stage_ones<kWave * WG>(a.g, words, s_ones, BITS == BITS_LDS && a.ones_burst);
         __syncthreads();
     }
     if (p0 >= a.n) return;
@@ -492,8 +521,12 @@ __device__ void fitness_body(const FitLaunch& a, const int blk, uint32_t* s_ones
             }
         }
     };
-    if (lds) steps(std::bool_constant<kCount>{});
-    else steps(std::false_type{});
+    if constexpr (BITS == BITS_EITHER) {
+        if (lds) steps(std::true_type{});
+        else steps(std::false_type{});
+    } else {
+        steps(std::bool_constant<BITS == BITS_LDS>{});
+    }
     // every lane added kU terms per particle in each step it ran (lanes past
     // the slice end added 0); remove their kGridBase parts, modulo 2^64
     const uint64_t terms = (uint64_t)kWave * kU * (uint64_t)(nfull + (jt < j1 ? 1 : 0));
@@ -627,23 +660,24 @@ __device__ void fitness_body_pl(const FitLaunch& a, const int blk) {
 constexpr int kPlWaves = 8;
 constexpr int kPlWideMinBlocks = 1024;
 
-// Wavefronts per workgroup of a points-across launch (they share the staged
-// brick bits): 8, with which 32 KB of bits leave the CU its full 32
-// wavefronts, for nearest lookups of launches that keep kPaWideMinBlocks
-// workgroups; else 4.  512^3, 10240 particles x 19200 points, 640 workgroups
-// of 8 per slice: 464 / 555 us (two rooms) with 8, 481 / 592 with 4, 463 /
-// 538 with 16; a 64^3 frame of 1024 particles (256 workgroups of 8): 10
+// Wavefronts per workgroup of a points-across launch: they share the staged
+// brick bits, and with 8 of them 32 KB of bits leave the CU its full 32
+// wavefronts.  8 for staged launches that keep kPaWideMinBlocks workgroups;
+// else 4.  512^3, 10240 particles x 19200 points, 320 workgroups of 8 per
+// slice: 464 / 555 us (two rooms) with 8, 481 / 592 with 4, 463 / 538 with 16
+// (not taken: a level of a few thousand particles leaves them too few
+// workgroups); a 64^3 frame of 1024 particles (256 workgroups of 8): 10
 // iterations 307 us with 8, 295 with 4.  Trilinear lookups stage nothing and
 // have the registers of 3 wavefronts per SIMD: 4 is 4 % faster there.
 constexpr int kPaWaves = 8;
 constexpr int kPaWideMinBlocks = 512;
+constexpr int kPaWideMinPoints = 192;
 
-template <int P, int U, int FMT, int LK, bool FROM_STATE, bool WIDE, bool ACC32 = false, int WG = 4>
+template <int P, int U, int FMT, int LK, bool FROM_STATE, bool WIDE, bool ACC32, int WG, int BITS>
 __global__ __launch_bounds__(kWave * WG) void k_fitness(FitLaunch a) {
-    extern __shared__ uint32_t s_dyn[];  // points across: the brick bits
+    extern __shared__ __attribute__((aligned(16))) uint32_t s_dyn[];  // points across: the brick bits
     if constexpr (P == kWave) fitness_body_pl<U, FMT, LK, FROM_STATE, WIDE, ACC32, WG>(a, blockIdx.x);
-    else
-        fitness_body<P, U, FMT, LK, FROM_STATE, WIDE, ACC32, WG>(a, blockIdx.x, a.ones_lds ? s_dyn : nullptr);
+    else fitness_body<P, U, FMT, LK, FROM_STATE, WIDE, ACC32, WG, BITS>(a, blockIdx.x, s_dyn);
 }
 
 // Work items of the persistent batch kernel: 4 or 8 particle groups
@@ -676,7 +710,7 @@ template <int P, int U, int FMT, int LK>
 __global__ __launch_bounds__(kWave * batch_waves(P, LK)) void k_fitness_batch(
     const FitLaunch* __restrict__ seqs, const int* __restrict__ begin, int count, int base, int end,
     int* __restrict__ ctr, int ones_lds) {
-    extern __shared__ uint32_t s_dyn[];
+    extern __shared__ __attribute__((aligned(16))) uint32_t s_dyn[];
     __shared__ int s_k;
     int last = -1;  // the sequence whose brick bits are staged
     const int xcd = (int)(blockIdx.x & 7u);
@@ -699,8 +733,9 @@ __global__ __launch_bounds__(kWave * batch_waves(P, LK)) void k_fitness_batch(
         // branch above is uniform over the workgroup (one item per workgroup)
         if constexpr (P == kWave) fitness_body_pl<U, FMT, LK, true, false>(L, blk);
         else {
-            fitness_body<P, U, FMT, LK, true, false, false, batch_waves(P, LK)>(L, blk, ones_lds ? s_dyn : nullptr,
-                                                                               lo == last);
+            fitness_body<P, U, FMT, LK, true, false, false, batch_waves(P, LK),
+                         LK == ROSE_LOOKUP_NEAREST ? BITS_EITHER : BITS_MEMORY>(L, blk, ones_lds ? s_dyn : nullptr,
+                                                                                lo == last);
             last = L.st->stopped ? -1 : lo;  // a stopped sequence's item stages nothing
         }
     }
@@ -710,7 +745,7 @@ __global__ __launch_bounds__(kWave * batch_waves(P, LK)) void k_fitness_batch(
 // read from memory, or not at all)
 int ones_lds_bytes(const Grid& g, int lk, int P) {
     const uint32_t w = ones_words(g);
-    return P != kWave && lk == ROSE_LOOKUP_NEAREST && w <= kOnesLdsWords ? (int)(4u * w) : 0;
+    return P != kWave && lk == ROSE_LOOKUP_NEAREST && w <= kOnesLdsWords ? (int)((4u * w + 15u) & ~15u) : 0;
 }
 
 // A persistent grid must fit on the device at once: workgroups that only
@@ -877,36 +912,53 @@ void fit_launch_shape(const rose_tsdf* h, int lk, int* p, int* u, float* thr_vox
     *zref_m = c.zref;
 }
 
-template <int P, int U, int FMT, int LK, bool WIDE, int WG>
-static void launch_pu_wg(const FitLaunch& Lin, unsigned blocks, hipStream_t s) {
-    const dim3 threads(kWave * WG);
-    FitLaunch L = Lin;
-    const unsigned lds = (WIDE || L.acc32) ? 0u : (unsigned)ones_lds_bytes(L.g, LK, P);
-    L.ones_lds = lds > 0;
+template <int P, int U, int FMT, int LK, bool WIDE, int WG, int BITS>
+static void launch_pu_wg(const FitLaunch& L, unsigned lds, hipStream_t s) {
+    const dim3 threads(kWave * WG), blocks((unsigned)blocks_of(L, P, WG));
     if (L.T32)
-        hipLaunchKernelGGL((k_fitness<P, U, FMT, LK, false, WIDE, false, WG>), dim3(blocks), threads, lds, s, L);
-    else if constexpr (FMT == ROSE_TSDF_F32 && !WIDE) {
+        hipLaunchKernelGGL((k_fitness<P, U, FMT, LK, false, WIDE, false, WG, BITS>), blocks, threads, lds, s, L);
+    else if constexpr (FMT == ROSE_TSDF_F32 && !WIDE && BITS == BITS_MEMORY) {
         if (L.acc32)
-            hipLaunchKernelGGL((k_fitness<P, U, FMT, LK, true, WIDE, true, WG>), dim3(blocks), threads, lds, s, L);
+            hipLaunchKernelGGL((k_fitness<P, U, FMT, LK, true, WIDE, true, WG, BITS>), blocks, threads, lds, s, L);
         else
-            hipLaunchKernelGGL((k_fitness<P, U, FMT, LK, true, WIDE, false, WG>), dim3(blocks), threads, lds, s, L);
+            hipLaunchKernelGGL((k_fitness<P, U, FMT, LK, true, WIDE, false, WG, BITS>), blocks, threads, lds, s, L);
     } else
-        hipLaunchKernelGGL((k_fitness<P, U, FMT, LK, true, WIDE, false, WG>), dim3(blocks), threads, lds, s, L);
+        hipLaunchKernelGGL((k_fitness<P, U, FMT, LK, true, WIDE, false, WG, BITS>), blocks, threads, lds, s, L);
 }
 
 template <int P, int U, int FMT, int LK, bool WIDE>
 static void launch_pu(const FitLaunch& L, hipStream_t s) {
     // points across: WG groups per workgroup and one slice; particle per
     // lane: WG groups of 64 per workgroup and one quarter-slice
-    constexpr int kWide = P == kWave ? kPlWaves : kPaWaves;
-    if constexpr (P == kWave || (LK == ROSE_LOOKUP_NEAREST && !WIDE)) {
-        const int wide = blocks_of(L, P, kWide);
-        if (wide >= (P == kWave ? kPlWideMinBlocks : kPaWideMinBlocks)) {
-            launch_pu_wg<P, U, FMT, LK, WIDE, kWide>(L, (unsigned)wide, s);
+    if constexpr (P == kWave) {
+        if (blocks_of(L, P, kPlWaves) >= kPlWideMinBlocks)
+            return launch_pu_wg<P, U, FMT, LK, WIDE, kPlWaves, BITS_MEMORY>(L, 0, s);
+    } else if constexpr (LK == ROSE_LOOKUP_NEAREST && !WIDE) {
+        // Launches that leave each CU few workgroups stage the brick bits, whose
+        // wait in LDS is the shorter one (512^3, 1 particle x 19000 points: 28
+        // us against 29 from memory, 64 x 19000: 37 / 39).  Larger ones do so
+        // while a slice has kPaWideMinPoints points (at most) or more: with
+        // fewer, the copy and the barrier cost more than the one or two steps
+        // save (10240 x 300: 31 us from memory, 33 with the burst below, 37
+        // with a word at a time; 384^3, 10240 x 1000: 37, 39, 41; 2000: 57,
+        // 55, 58).
+        // The copy: a burst, or a word per thread and round.  Below 3
+        // evaluations per word its latency counts (10240 x 4000: 73 / 113 us
+        // near / wide poses with the burst, 77 / 122 without); from there on,
+        // where workgroups follow one another on a CU, the slow copy spreads
+        // their starts (10240 x 19000: 512 / 595 us, 498 / 588).
+        const int lds = L.acc32 ? 0 : ones_lds_bytes(L.g, LK, P);
+        const bool wide = blocks_of(L, P, kPaWaves) >= kPaWideMinBlocks;
+        if (lds > 0 && (!wide || L.count >= kPaWideMinPoints * L.splits)) {
+            const int64_t particles = std::min(P * (wide ? kPaWaves : 4), L.n);
+            FitLaunch B = L;
+            B.ones_burst = particles * ((L.count + L.splits - 1) / L.splits) < 3 * (int64_t)(lds / 4);
+            if (wide) launch_pu_wg<P, U, FMT, LK, WIDE, kPaWaves, BITS_LDS>(B, (unsigned)lds, s);
+            else launch_pu_wg<P, U, FMT, LK, WIDE, 4, BITS_LDS>(B, (unsigned)lds, s);
             return;
         }
     }
-    launch_pu_wg<P, U, FMT, LK, WIDE, 4>(L, (unsigned)blocks_of(L, P, 4), s);
+    launch_pu_wg<P, U, FMT, LK, WIDE, 4, BITS_MEMORY>(L, 0, s);
 }
 
 template <int FMT, int LK>

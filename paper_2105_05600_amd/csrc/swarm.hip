@@ -367,6 +367,7 @@ static rose_status swarm_track(rose_tsdf* h, const float* depth_dev, const rose_
     fl.g = h->g;
     fl.pts = h->pts_o;
     fl.count_dev = &h->st->n_overlap;
+    fl.count = (int32_t)mmax;
     fl.T32 = nullptr;
     fl.st = h->st;
     fl.lookup = p->lookup;

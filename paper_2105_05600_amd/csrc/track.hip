@@ -814,6 +814,7 @@ rose_status pso_track_frame(rose_tsdf* h, const float* depth_dev, const float* p
         fl.n = lv_n[l];
         fl.order = lv_order[l];
         fl.splits = lv_splits[l];
+        fl.count = (int32_t)(lv_off[l + 1] - lv_off[l]);
         ua.n = lv_n[l];
         ua.splits = lv_splits[l];
         ua.pts = h->pts + lv_off[ln];
@@ -1152,6 +1153,7 @@ rose_status pso_batch_create(int32_t count, rose_tsdf* const* tsdfs, const rose_
         L.g = h->g;
         L.pts = h->pts_o;
         L.count_dev = &h->st->n_overlap;
+        L.count = (int32_t)mmax;
         L.T32 = nullptr;
         L.st = h->st;
         L.pst = pst_devs[i];
