@@ -964,11 +964,18 @@ static void launch_pu(const FitLaunch& L, hipStream_t s) {
 template <int FMT, int LK>
 static void launch_w(const FitLaunch& L, hipStream_t s) {
     const uint64_t bytes = (uint64_t)L.g.nx * L.g.ny * L.g.nz * (FMT == ROSE_TSDF_F32 ? 4u : 2u);
-    if (bytes >= (uint64_t(1) << 32)) {
+    const int p = L.shape_p, u = L.shape_u;
+    // 16-bit interpolated lookups take their corners one by one, through plain
+    // pointers as in volumes past 4 GB, where a wavefront has only a step or
+    // two or few wavefronts run: the pairs' decoding makes each step longer
+    // (4096 particles x 300 points: 28.5 us one by one, 33 in pairs; 1 x 4000:
+    // 16.2 and 17.8; 4096 x 2000: 75 and 55)
+    const bool few = FMT != ROSE_TSDF_F32 && LK == ROSE_LOOKUP_TRILINEAR && p == 4 && u == 2 &&
+                     (L.count < kPaWideMinPoints * L.splits || L.n <= 16);
+    if (few || bytes >= (uint64_t(1) << 32)) {
         launch_pu<4, 2, FMT, LK, true>(L, s);
         return;
     }
-    const int p = L.shape_p, u = L.shape_u;
     if (p == 2 && u == 4) launch_pu<2, 4, FMT, LK, false>(L, s);
     else if (p == 4 && u == 4) launch_pu<4, 4, FMT, LK, false>(L, s);
     else if (p == 4 && u == 8) launch_pu<4, 8, FMT, LK, false>(L, s);
