@@ -964,7 +964,11 @@ static void launch_pu(const FitLaunch& L, hipStream_t s) {
 template <int FMT, int LK>
 static void launch_w(const FitLaunch& L, hipStream_t s) {
     const uint64_t bytes = (uint64_t)L.g.nx * L.g.ny * L.g.nz * (FMT == ROSE_TSDF_F32 ? 4u : 2u);
-    const int p = L.shape_p, u = L.shape_u;
+    int p = L.shape_p, u = L.shape_u;
+    // a single wavefront's particles one per lane: interpolated lookups wait
+    // for their pairs with nothing else to do (1 particle x 4000 points: 51 us,
+    // 16 with the points across the lanes; 36 with one load per corner)
+    if (LK == ROSE_LOOKUP_TRILINEAR && p == kWave && L.pl_side == 0 && L.n <= kWave) p = 4, u = 2;
     // 16-bit interpolated lookups take their corners one by one, through plain
     // pointers as in volumes past 4 GB, where a wavefront has only a step or
     // two or few wavefronts run: the pairs' decoding makes each step longer
