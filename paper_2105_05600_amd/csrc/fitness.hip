@@ -191,6 +191,13 @@ __device__ inline bool nearest_offset(const Grid& g, const VoxelTest& e, float g
 // iterations: 2735 -> 2140 us; 512^3 binary32, 10240 x 19200: 2310 -> 1660
 // us.  The 16-bit formats read the 4 values from the 4-byte boundary at
 // or below the first one (mis: the buffer's own offset from such a boundary).
+// ANY (a tracked frame's particles one per lane, binary32): wavefronts without
+// a lane at a brick boundary skip the 4 masked loads, which pays where the
+// poses are alike (64 / 1000 particles of a 160 x 120 frame in 128^3, 6
+// iterations: 347 / 354 -> 281 / 306 us; one load per corner 308 / 338).  With
+// the points across the lanes, with 16 bits and for poses far apart (512^3,
+// 4096 poses over half a metre x 2000 points: 105 and 124 us) the branch costs
+// more than it saves.
 struct TriCell {
     float fx, fy, fz;
     bool in, split;
@@ -203,7 +210,7 @@ __device__ inline float psi_of_bits(uint32_t b) {
     else return (float)(int16_t)b * (1.0f / 32767.0f);
 }
 
-template <int FMT, bool WIDE>
+template <int FMT, bool WIDE, bool ANY>
 __device__ inline void tri_load(const Grid& g, const PsiBuf& b, float gx, float gy, float gz, TriCell& c) {
     const float hx = gx - 0.5f, hy = gy - 0.5f, hz = gz - 0.5f;
     c.in = (hx >= 0.0f) & (hx < (float)(g.nx - 1)) & (hy >= 0.0f) & (hy < (float)(g.ny - 1)) & (hz >= 0.0f) &
@@ -217,6 +224,7 @@ __device__ inline void tri_load(const Grid& g, const PsiBuf& b, float gx, float 
     const uint32_t dy = (iy & 7u) == 7u ? 512u * (uint32_t)g.nbx - 56u : 8u;
     const uint32_t dz = (iz & 7u) == 7u ? 512u * (uint32_t)g.nbx * (uint32_t)g.nby - 448u : 64u;
     const uint32_t o = brick_offset(g, ix, iy, iz);
+    const bool any = !ANY || __builtin_amdgcn_ballot_w64(c.split) != 0;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
         const uint32_t row = o + ((e & 1) ? dy : 0u) + ((e >> 1) ? dz : 0u);
@@ -236,7 +244,7 @@ __device__ inline void tri_load(const Grid& g, const PsiBuf& b, float gx, float 
                 c.v[2 * e] = psi_of_bits<FMT>(p & 0xffffu);
                 c.v[2 * e + 1] = psi_of_bits<FMT>(p >> 16);
             }
-            c.w[e] = gather_bytes<FMT>(b, c.split ? elem_bytes<FMT>() * (row + 505u) : 0xfffffffcu);
+            if (any) c.w[e] = gather_bytes<FMT>(b, c.split ? elem_bytes<FMT>() * (row + 505u) : 0xfffffffcu);
         }
     }
 #pragma unroll
@@ -282,7 +290,7 @@ __device__ inline bool switch_skips(const FitLaunch& a) {
 // voxel containing it (+1 outside the grid), TRILINEAR interpolates.
 // Evaluations are done in batches of K: all K addresses first, then all K
 // gathers (in flight together), then the selects.
-template <int K, int FMT, int LK, bool WIDE>
+template <int K, int FMT, int LK, bool WIDE, bool ANY = false>
 __device__ inline void psi_batch(const Grid& g, const PsiBuf& b, const VoxelTest& ext, const float (&gx)[K],
                                  const float (&gy)[K], const float (&gz)[K], float (&v)[K]) {
     if constexpr (LK == ROSE_LOOKUP_NEAREST) {
@@ -308,7 +316,7 @@ __device__ inline void psi_batch(const Grid& g, const PsiBuf& b, const VoxelTest
         for (int k0 = 0; k0 < K; k0 += kB) {
             TriCell c[kB];
 #pragma unroll
-            for (int k = 0; k < kB; ++k) tri_load<FMT, WIDE>(g, b, gx[k0 + k], gy[k0 + k], gz[k0 + k], c[k]);
+            for (int k = 0; k < kB; ++k) tri_load<FMT, WIDE, ANY>(g, b, gx[k0 + k], gy[k0 + k], gz[k0 + k], c[k]);
 #pragma unroll
             for (int k = 0; k < kB; ++k) v[k0 + k] = tri_value(c[k]);
             __builtin_amdgcn_sched_barrier(0);  // keeps the next ones' loads out of this one's registers
@@ -568,7 +576,7 @@ __device__ void fitness_body(const FitLaunch& a, const int blk, uint32_t* s_ones
 // Slices and their XCD mapping are those of fitness_body counted in
 // quarters (XCD x owns the contiguous quarter-slices x 4S/8 ...).  Every
 // exit before a barrier is uniform over the workgroup.
-template <int U, int FMT, int LK, bool FROM_STATE, bool WIDE, bool ACC32 = false, int WG = 4>
+template <int U, int FMT, int LK, bool FROM_STATE, bool WIDE, bool ACC32 = false, int WG = 4, bool ANY = false>
 __device__ void fitness_body_pl(const FitLaunch& a, const int blk) {
     __shared__ float4 s_pts[kWave];
     const int lane = threadIdx.x & 63;
@@ -623,7 +631,7 @@ __device__ void fitness_body_pl(const FitLaunch& a, const int blk) {
             gy[u] = xf_row(V[4], V[5], V[6], V[7], x.x, x.y, x.z);
             gz[u] = xf_row(V[8], V[9], V[10], V[11], x.x, x.y, x.z);
         }
-        psi_batch<K, FMT, LK, WIDE>(g, pb, ext, gx, gy, gz, v);
+        psi_batch<K, FMT, LK, WIDE, ANY>(g, pb, ext, gx, gy, gz, v);
 #pragma unroll
         for (int u = 0; u < K; ++u) add_sq<ACC32>(acc, accf, v[u]);
     };
@@ -676,7 +684,8 @@ constexpr int kPaWideMinPoints = 192;
 template <int P, int U, int FMT, int LK, bool FROM_STATE, bool WIDE, bool ACC32, int WG, int BITS>
 __global__ __launch_bounds__(kWave * WG) void k_fitness(FitLaunch a) {
     extern __shared__ __attribute__((aligned(16))) uint32_t s_dyn[];  // points across: the brick bits
-    if constexpr (P == kWave) fitness_body_pl<U, FMT, LK, FROM_STATE, WIDE, ACC32, WG>(a, blockIdx.x);
+    if constexpr (P == kWave)
+        fitness_body_pl<U, FMT, LK, FROM_STATE, WIDE, ACC32, WG, FROM_STATE && !WIDE && FMT == ROSE_TSDF_F32>(a, blockIdx.x);
     else fitness_body<P, U, FMT, LK, FROM_STATE, WIDE, ACC32, WG, BITS>(a, blockIdx.x, s_dyn);
 }
 
