@@ -92,11 +92,6 @@ __device__ inline int level_samples(const InitStatic& a, int l) {
     return sample_count((a.cam.W + a.stride[l] - 1) / a.stride[l], (a.cam.H + a.stride[l] - 1) / a.stride[l], true);
 }
 
-// points that a level's list has room for
-__device__ inline int level_capacity(const InitStatic& a, int l) {
-    return ((a.cam.W + a.stride[l] - 1) / a.stride[l]) * ((a.cam.H + a.stride[l] - 1) / a.stride[l]);
-}
-
 // Unprojection of the frame at every resolution level, device-state
 // initialisation and the first overlap set (level 0), in 8x8-sample tile
 // order: a workgroup per 1024 samples of a level, or one for all.  One
@@ -196,7 +191,7 @@ __device__ void track_init_body(const InitStatic& a, const FrameIn& in, int bloc
         }
     }
     __syncthreads();
-    const int cap = level_capacity(a, l);
+    const int cap = a.cap[l];
     const int at = keep ? list_slot(before, 0, pos, cap) : -1, at_o = over ? list_slot(before, 1, po, cap) : -1;
     if (at >= 0) a.pts[a.offset[l] + at] = x;
     if (at_o >= 0) a.pts_o[at_o] = x;
@@ -206,14 +201,14 @@ __device__ void track_init_body(const InitStatic& a, const FrameIn& in, int bloc
             const int np = (level_samples(a, k) + 1023) / 1024;
             const uint64_t m = counts_before(a.work, o, p, p + np);
             p += np;
-            const int n_k = list_size(m, 0, level_capacity(a, k));
+            const int n_k = list_size(m, 0, a.cap[k]);
             any += n_k > 0;
             if (lane == 0) {
                 if (m == kCountsLost) a.st->status = 1;
                 a.st->lvl_points[k] = n_k;
                 if (k == 0) {
                     a.st->n_points = n_k;
-                    a.st->n_overlap = list_size(m, 1, level_capacity(a, 0));
+                    a.st->n_overlap = list_size(m, 1, a.cap[0]);
                 }
             }
         }

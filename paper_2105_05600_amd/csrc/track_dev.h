@@ -186,15 +186,18 @@ struct InitStatic {
     int32_t flags;
     int32_t stride[ROSE_MAX_LEVELS];       // subsampling stride per level
     int32_t offset[ROSE_MAX_LEVELS];       // first point of each level in pts
+    int32_t cap[ROSE_MAX_LEVELS];          // points that each level's list has room for (init_blocks)
     float4* pts;
     float4* pts_o;
 };
 
-// workgroups of the init launch: 1024 padded samples of one level each
-inline int init_blocks(const InitStatic& a) {
+// workgroups of the init launch: 1024 padded samples of one level each; sets
+// the levels' capacities
+inline int init_blocks(InitStatic& a) {
     int64_t b = 0;
     for (int l = 0; l < a.levels; ++l) {
         const int su = (a.cam.W + a.stride[l] - 1) / a.stride[l], sv = (a.cam.H + a.stride[l] - 1) / a.stride[l];
+        a.cap[l] = su * sv;
         b += ((int64_t)((su + 7) / 8) * ((sv + 7) / 8) * 64 + 1023) / 1024;
     }
     return b <= kMaxParts ? (int)std::max<int64_t>(b, 1) : 1;
