@@ -943,25 +943,28 @@ static void launch_pu(const FitLaunch& L, hipStream_t s) {
         if (blocks_of(L, P, kPlWaves) >= kPlWideMinBlocks)
             return launch_pu_wg<P, U, FMT, LK, WIDE, kPlWaves, BITS_MEMORY>(L, 0, s);
     } else if constexpr (LK == ROSE_LOOKUP_NEAREST && !WIDE) {
-        // Launches that leave each CU few workgroups stage the brick bits, whose
-        // wait in LDS is the shorter one (512^3, 1 particle x 19000 points: 28
-        // us against 29 from memory, 64 x 19000: 37 / 39).  Larger ones do so
-        // while a slice has kPaWideMinPoints points (at most) or more: with
-        // fewer, the copy and the barrier cost more than the one or two steps
-        // save (10240 x 300: 31 us from memory, 33 with the burst below, 37
-        // with a word at a time; 384^3, 10240 x 1000: 37, 39, 41; 2000: 57,
-        // 55, 58).
+        // The brick bits are staged while a slice has kPaWideMinPoints points
+        // (at most) or more: with fewer, the copy and the barrier cost more
+        // than the one or two steps save (10240 x 300: 31 us from memory, 33
+        // with the burst below, 37 with a word at a time; 384^3, 10240 x 1000:
+        // 37, 39, 41; 2000: 57, 55, 58; 512^3, 1 x 19000, whose wait in LDS is
+        // the shorter one: 29, 28, 30), but bits that take a round or two of 4
+        // wavefronts cost next to nothing (128^3, 6 iterations of 1000 x 1200:
+        // 199 us from memory, 190).
         // The copy: a burst, or a word per thread and round.  Below 3
-        // evaluations per word its latency counts (10240 x 4000: 73 / 113 us
-        // near / wide poses with the burst, 77 / 122 without); from there on,
-        // where workgroups follow one another on a CU, the slow copy spreads
-        // their starts (10240 x 19000: 512 / 595 us, 498 / 588).
+        // evaluations per word, with more than two rounds, its latency counts
+        // (10240 x 4000: 73 / 113 us near / wide poses with the burst, 77 /
+        // 122 without); from there on, where workgroups follow one another on
+        // a CU, the slow copy spreads their starts (10240 x 19000: 512 / 595
+        // us, 498 / 588).
         const int lds = L.acc32 ? 0 : ones_lds_bytes(L.g, LK, P);
-        const bool wide = blocks_of(L, P, kPaWaves) >= kPaWideMinBlocks;
-        if (lds > 0 && (!wide || L.count >= kPaWideMinPoints * L.splits)) {
-            const int64_t particles = std::min(P * (wide ? kPaWaves : 4), L.n);
+        const bool full = L.count >= kPaWideMinPoints * L.splits, small = lds / 4 <= 2 * kWave * 4;
+        if (lds > 0 && (full || (small && L.count >= kWave * L.splits))) {
+            const bool wide = full && blocks_of(L, P, kPaWaves) >= kPaWideMinBlocks;
+            const int waves = wide ? kPaWaves : 4;
+            const int64_t evals = (int64_t)std::min(P * waves, L.n) * ((L.count + L.splits - 1) / L.splits);
             FitLaunch B = L;
-            B.ones_burst = particles * ((L.count + L.splits - 1) / L.splits) < 3 * (int64_t)(lds / 4);
+            B.ones_burst = evals < 3 * (int64_t)(lds / 4) && lds / 4 > 2 * kWave * waves;
             if (wide) launch_pu_wg<P, U, FMT, LK, WIDE, kPaWaves, BITS_LDS>(B, (unsigned)lds, s);
             else launch_pu_wg<P, U, FMT, LK, WIDE, 4, BITS_LDS>(B, (unsigned)lds, s);
             return;
@@ -979,12 +982,13 @@ static void launch_w(const FitLaunch& L, hipStream_t s) {
     // 16 with the points across the lanes; 36 with one load per corner)
     if (LK == ROSE_LOOKUP_TRILINEAR && p == kWave && L.pl_side == 0 && L.n <= kWave) p = 4, u = 2;
     // 16-bit interpolated lookups take their corners one by one, through plain
-    // pointers as in volumes past 4 GB, where a wavefront has only a step or
-    // two or few wavefronts run: the pairs' decoding makes each step longer
+    // pointers as in volumes past 4 GB, where a wavefront has only one step
+    // or few wavefronts run: the pairs' decoding makes each step longer
     // (4096 particles x 300 points: 28.5 us one by one, 33 in pairs; 1 x 4000:
-    // 16.2 and 17.8; 4096 x 2000: 75 and 55)
+    // 16.2 and 17.8; 4096 x 2000: 75 and 55; 6 iterations of 1000 x 1200: 226
+    // and 205)
     const bool few = FMT != ROSE_TSDF_F32 && LK == ROSE_LOOKUP_TRILINEAR && p == 4 && u == 2 &&
-                     (L.count < kPaWideMinPoints * L.splits || L.n <= 16);
+                     (L.count <= 2 * kWave * L.splits || L.n <= 16);
     if (few || bytes >= (uint64_t(1) << 32)) {
         launch_pu<4, 2, FMT, LK, true>(L, s);
         return;

@@ -14,7 +14,7 @@ torch = pytest.importorskip("torch")
 @pytest.mark.parametrize("fmt", [0, 2])
 @pytest.mark.parametrize("shape", [(4, 2), (8, 4)])
 @pytest.mark.parametrize("dims", [(72, 72, 72), (512, 512, 512), (264, 264, 8)])
-@pytest.mark.parametrize("m,n", [(1535, 4096), (1536, 4097), (1537, 8200), (1536, 1000), (90, 4096), (5000, 3), (5000, 130)])
+@pytest.mark.parametrize("m,n", [(1535, 4096), (1536, 4097), (1537, 8200), (1536, 1000), (511, 4096), (512, 4096), (90, 4096), (5000, 3), (5000, 130)])
 def test_bits_paths(dims, m, n, shape, fmt):
     from paper_2105_05600_amd import rose
     vol, psi = _volume(dims, 0.02, fmt, m + n)

@@ -13,7 +13,7 @@ torch = pytest.importorskip("torch")
 
 
 @pytest.mark.parametrize("fmt", [0, 1, 2])
-@pytest.mark.parametrize("m,n", [(1535, 300), (1536, 300), (1537, 300), (4000, 16), (4000, 17), (4000, 64), (4000, 65), (90, 1), (3, 700)])
+@pytest.mark.parametrize("m,n", [(1024, 300), (1025, 300), (1537, 300), (4000, 16), (4000, 17), (4000, 64), (4000, 65), (90, 1), (3, 700)])
 def test_fitness_routes(m, n, fmt):
     from paper_2105_05600_amd import rose
     vol, psi = _volume((72, 40, 56), 0.02, fmt, m + n)
