@@ -64,11 +64,10 @@ __device__ inline bool brick_all_ones(const PsiBuf& b, uint32_t off) {
 
 // The brick bits of volumes up to 512^3 (kOnesLdsWords words) are staged in
 // LDS by the points-across kernels: read through the vector memory path the
-// word of an evaluation costs as much of its cache-access rate as 16 of the
-// gather's lines (a quarter of all accesses on the wide search), and that rate
-// is what bounds the kernel (its data return busy 99 % of the time).  512^3,
-// 10240 particles x 19200 points, axis lengths 0.005 / 0.05 / 0.15: 366 / 409 /
-// 355 us -> 287 / 385 / 330; the bench's points-across steps 0.632 -> 0.598 ms.
+// word of an evaluation is one more access beside its voxel's, and the rate of
+// these accesses is what bounds the kernel (arithmetic taken out changed
+// nothing).  512^3, 10240 particles x 19200 points, axis lengths 0.005 / 0.05 /
+// 0.15: 366 / 409 / 355 us -> 287 / 385 / 330.
 constexpr uint32_t kOnesLdsWords = 8192;  // 32 KB
 
 __host__ __device__ inline uint32_t ones_words(const Grid& g) {
@@ -350,7 +349,7 @@ __device__ void fitness_body(const FitLaunch& a, const int blk, uint32_t* s_ones
     // of the point list, so its L2 only holds the voxels around those
     // points; its workgroups cycle through those slices before moving to the
     // next particles, so the particles in flight on an XCD are few (and, in
-    // the schedule order, similar).  The 4 waves of a workgroup take 4
+    // the schedule order, similar).  The WG waves of a workgroup take
     // consecutive particle groups of the same slice (shared point loads and
     // nearby gathers in the CU's L1).
     const int s8 = a.splits >> 3;

@@ -486,8 +486,12 @@ static int32_t tile_span(int64_t srow, int64_t sk, int32_t rows, int32_t ks, int
 //   512^2 x 2048  64: 27, small: 20; 1024 x 256 x 1216  64: 18, small: 15
 //   4096^2 x 128  256: 41, 128: 33, 64: 23 (few k-steps: the stores count,
 //   and more workgroups overlap them with other tiles' products)
-// so a wider tile is taken once it leaves (almost) every CU a workgroup --
-// two of them with 128 x 128, whose waves alone do not hide their loads.
+//   between these, K = 2048, 256 / 128 / 64:  2048^2 107 / 59 / 58 (K = 512:
+//   48 / 24 / 19), 3072 x 2048 107 / 60 / 78, 4096 x 3072 108 / 98 / 152, 3584^2
+//   108 / 119 / 152, 4352 x 4096 213 / 142 / 208, 4608^2 213 / 172 / 244
+// so a wider tile is taken once it leaves (almost) every CU a workgroup.  The
+// last round of workgroups is not looked at: just past 256 tiles of 256 the
+// 128-square tile would be the faster one, at 256 tiles of 128 the 64-square.
 template <int LA, int LB>
 static void launch_gemm(GemmArgs g, hipStream_t s) {
     auto tiles = [&](int t) { return (int64_t)((g.M + t - 1) / t) * ((g.N + t - 1) / t); };

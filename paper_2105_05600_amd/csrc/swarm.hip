@@ -97,7 +97,6 @@ __global__ __launch_bounds__(1024) void k_swarm_best(SwarmArgs a, int k) {
     __shared__ float A[12];
     __shared__ float s_Fb;
     __shared__ int go_on;
-    __shared__ int lds[17];
     DevState* ch = a.chart;
     if (ch->stopped) return;  // the frame has no valid point
     const int n = a.n;
@@ -186,8 +185,7 @@ __global__ __launch_bounds__(1024) void k_swarm_best(SwarmArgs a, int k) {
             a.C[i] = acc;
         }
     }
-    const int nO = overlap_compact(a.cam, A, (a.flags & ROSE_FLAG_NO_OVERLAP) != 0, a.pts, ch->n_points, a.pts_o,
-                                   lds);
+    const int nO = overlap_compact(a.cam, A, (a.flags & ROSE_FLAG_NO_OVERLAP) != 0, a.pts, ch->n_points, a.pts_o);
     if (threadIdx.x == 0) ch->n_overlap = nO;
 }
 

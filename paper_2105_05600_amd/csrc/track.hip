@@ -391,7 +391,7 @@ __device__ inline void pst_update(const UpdateArgs& a, StepState& s, const doubl
 // both launches 19 us per iteration, against 32 us for a reduction launch and
 // one workgroup that did the rest; the 32 frames of a batch: 21 against 36 us.
 __device__ void track_step_body(const UpdateArgs& a, int block) {
-    __shared__ int lds[17];
+    __shared__ int lds[16];
     __shared__ uint64_t before;
     __shared__ double red[16][9], tot[9];
     __shared__ float A[12];
@@ -513,7 +513,7 @@ __device__ void track_step_body(const UpdateArgs& a, int block) {
     const int m = min(s.lvl_points[a.next_level], a.pts_cap);
     const bool all = (a.flags & ROSE_FLAG_NO_OVERLAP) != 0;
     if (a.blocks == 1) {
-        const int n = overlap_compact(a.cam, A, all, a.pts, m, a.pts_o, lds);
+        const int n = overlap_compact(a.cam, A, all, a.pts, m, a.pts_o);
         if (tid == 0) a.st->n_overlap = n;
         return;
     }
@@ -863,12 +863,12 @@ rose_status pso_track_frame(rose_tsdf* h, const float* depth_dev, const float* p
 }  // extern "C"
 
 // ------------------------------------------------------------------ batching
-// Many sequences tracked in lockstep: per frame step one init launch (one
-// workgroup per sequence), then per iteration one persistent fitness launch
-// per group over the small sequences' work, the fitness launches of each
-// large switching-mode sequence (the single path's), one slice-reduction
-// launch and one update launch (one workgroup per sequence), then one
-// launch copying the states to pinned host memory.  The
+// Many sequences tracked in lockstep: per frame step one init launch (a
+// column of workgroups per sequence), then per iteration one persistent
+// fitness launch per group over the small sequences' work, the fitness
+// launches of each large switching-mode sequence (the single path's), one
+// launch for the APS terms and one for the step (columns of workgroups each),
+// then one launch copying the states to pinned host memory.  The
 // sequence of launches is captured once into a HIP graph and replayed every
 // frame step; per-frame inputs are read by the init kernel from pinned host
 // memory, so the graph itself never changes.

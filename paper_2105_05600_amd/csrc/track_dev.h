@@ -67,10 +67,8 @@ __device__ inline bool sample_at(int q, int su, int sv, bool tiled, int* uu, int
 // tests its point of each round (all loads in flight together), the waves'
 // ballots give per-round, per-wave counts, one table in LDS turns them into
 // output offsets, and each thread writes its kept points.  The output is the
-// kept points in index order.  (lds is unused; kept for the callers' shape.)
-__device__ inline int overlap_compact(const Cam& c, const float* A, bool all, const float4* pts, int m, float4* out,
-                                      int* lds) {
-    (void)lds;
+// kept points in index order.
+__device__ inline int overlap_compact(const Cam& c, const float* A, bool all, const float4* pts, int m, float4* out) {
     constexpr int kRounds = 8, kMaxWaves = 16;
     __shared__ int cnt[kMaxWaves * kRounds];   // wave w, round q: kept count, then exclusive wave offset
     __shared__ int start[kRounds + 1];         // round offsets; start[kRounds] = batch total
