@@ -475,11 +475,11 @@ FitConfig fit_config(const rose_tsdf* h);
 // launches use for lookup lk: the fixed shape, or in the switching mode the
 // points-across side (its wide shape; (4, 2) for trilinear lookups).
 void fit_launch_shape(const rose_tsdf* h, int lk, int* p, int* u, float* thr_vox, float* zref_m);
-int fitness_blocks(const FitLaunch& L, int P);
+int fitness_blocks(const FitLaunch& L, int P, int U);
 bool batch_shape_valid(int p, int u);
 int batch_grid(int P, int U, int fmt, int lk, int requested, int lds);
-// LDS bytes that a points-across launch of shape P takes for a volume's brick bits (0: none)
-int ones_lds_bytes(const Grid& g, int lk, int P);
+// LDS bytes that the persistent batch launch takes for a volume's brick bits (0: none)
+int batch_lds_bytes(const Grid& g, int lk, int P, int U);
 // ctr_dev: the group's 8 per-XCD work counters, zero at launch
 rose_status launch_fitness_batch(const FitLaunch* seqs_dev, const int* begin_dev, int count, int base, int end,
                                  int grid, int lds, int P, int U, int fmt, int lk, int* ctr_dev, hipStream_t s);

@@ -690,15 +690,21 @@ __global__ __launch_bounds__(kWave * WG) void k_fitness(FitLaunch a) {
 
 // Work items of the persistent batch kernel: 4 or 8 particle groups
 // (batch_waves) and one slice (points across the lanes), or 4 groups of 64
-// and one quarter of a slice (one particle per lane).
-constexpr int batch_waves(int P, int lk) { return P != kWave && lk == ROSE_LOOKUP_NEAREST ? kPaWaves : 4; }
+// and one quarter of a slice (one particle per lane).  8 with the brick bits
+// staged; shapes of more than 16 evaluations per lane and step hold them in
+// memory, with 4: two bodies in one kernel leave those too few registers (64
+// sequences in 128^3, 8 iterations: 4 x 8 6.8 ms with both, 5.1 without, 8 x 4
+// 4.7 and 3.7; 4 x 2 3.4 and 3.8).
+constexpr int batch_waves(int P, int U, int lk) {
+    return P != kWave && P * U <= 16 && lk == ROSE_LOOKUP_NEAREST ? kPaWaves : 4;
+}
 
 __host__ __device__ inline int blocks_of(const FitLaunch& L, int P, int waves) {
     const int groups = (L.n + P - 1) / P;
     return (groups + waves - 1) / waves * (P == kWave ? kPartSub : 1) * L.splits;
 }
 
-int fitness_blocks(const FitLaunch& L, int P) { return blocks_of(L, P, batch_waves(P, L.lookup)); }
+int fitness_blocks(const FitLaunch& L, int P, int U) { return blocks_of(L, P, batch_waves(P, U, L.lookup)); }
 
 // Persistent fitness over many tracked sequences of one storage format and
 // lookup (a batch launches one kernel per such group, so each kernel holds a
@@ -715,7 +721,7 @@ int fitness_blocks(const FitLaunch& L, int P) { return blocks_of(L, P, batch_wav
 // launch on the stream clears them, and every workgroup leaves once its
 // queue passes `end`.
 template <int P, int U, int FMT, int LK>
-__global__ __launch_bounds__(kWave * batch_waves(P, LK)) void k_fitness_batch(
+__global__ __launch_bounds__(kWave * batch_waves(P, U, LK)) void k_fitness_batch(
     const FitLaunch* __restrict__ seqs, const int* __restrict__ begin, int count, int base, int end,
     int* __restrict__ ctr, int ones_lds) {
     extern __shared__ __attribute__((aligned(16))) uint32_t s_dyn[];
@@ -736,13 +742,13 @@ __global__ __launch_bounds__(kWave * batch_waves(P, LK)) void k_fitness_batch(
         }
         const FitLaunch L = seqs[lo];  // wave-uniform: scalar loads of read-only memory
         const int blk = w - begin[lo];
-        if (blk >= blocks_of(L, P, batch_waves(P, LK))) continue;
+        if (blk >= blocks_of(L, P, batch_waves(P, U, LK))) continue;
         // the particle-per-lane body synchronises its workgroup once; every
         // branch above is uniform over the workgroup (one item per workgroup)
         if constexpr (P == kWave) fitness_body_pl<U, FMT, LK, true, false>(L, blk);
         else {
-            fitness_body<P, U, FMT, LK, true, false, false, batch_waves(P, LK),
-                         LK == ROSE_LOOKUP_NEAREST ? BITS_EITHER : BITS_MEMORY>(L, blk, ones_lds ? s_dyn : nullptr,
+            fitness_body<P, U, FMT, LK, true, false, false, batch_waves(P, U, LK),
+                         batch_waves(P, U, LK) == kPaWaves ? BITS_EITHER : BITS_MEMORY>(L, blk, ones_lds ? s_dyn : nullptr,
                                                                                 lo == last);
             last = L.st->stopped ? -1 : lo;  // a stopped sequence's item stages nothing
         }
@@ -754,6 +760,10 @@ __global__ __launch_bounds__(kWave * batch_waves(P, LK)) void k_fitness_batch(
 int ones_lds_bytes(const Grid& g, int lk, int P) {
     const uint32_t w = ones_words(g);
     return P != kWave && lk == ROSE_LOOKUP_NEAREST && w <= kOnesLdsWords ? (int)((4u * w + 15u) & ~15u) : 0;
+}
+
+int batch_lds_bytes(const Grid& g, int lk, int P, int U) {
+    return batch_waves(P, U, lk) == kPaWaves ? ones_lds_bytes(g, lk, P) : 0;
 }
 
 // A persistent grid must fit on the device at once: workgroups that only
@@ -774,14 +784,14 @@ static int resident_grid(K kernel, int requested, int threads, int lds) {
 template <int P, int U, int FMT, int LK>
 static void launch_batch_kernel(const FitLaunch* seqs, const int* begin, int count, int base, int end, int grid,
                                 int lds, int* ctr, hipStream_t s) {
-    hipLaunchKernelGGL((k_fitness_batch<P, U, FMT, LK>), dim3(grid), dim3(kWave * batch_waves(P, LK)),
+    hipLaunchKernelGGL((k_fitness_batch<P, U, FMT, LK>), dim3(grid), dim3(kWave * batch_waves(P, U, LK)),
                        LK == ROSE_LOOKUP_NEAREST ? (unsigned)lds : 0u, s, seqs, begin, count, base, end, ctr,
                        LK == ROSE_LOOKUP_NEAREST && lds > 0);
 }
 
 template <int P, int U>
 static int batch_grid_shape(int fmt, int lk, int requested, int lds) {
-    const int threads = kWave * batch_waves(P, lk);
+    const int threads = kWave * batch_waves(P, U, lk);
     if (lk == ROSE_LOOKUP_TRILINEAR) lds = 0;
     if (fmt == ROSE_TSDF_F32)
         return lk == ROSE_LOOKUP_TRILINEAR

@@ -1161,7 +1161,7 @@ rose_status pso_batch_create(int32_t count, rose_tsdf* const* tsdfs, const rose_
         L.pl_thr = shp_thr;
         L.pl_zref = shp_zref;
         L.partial = h->partial;
-        nblk[pos[i]] = own[i] ? 0 : fitness_blocks(L, P);
+        nblk[pos[i]] = own[i] ? 0 : fitness_blocks(L, P, U);
         if (own[i]) {
             b->own_of[i] = (int)b->own.size();
             b->own.push_back(i);
@@ -1227,7 +1227,7 @@ rose_status pso_batch_create(int32_t count, rose_tsdf* const* tsdfs, const rose_
         gr.base = begin[k];
         gr.end = begin[e];
         gr.lds = 0;
-        for (int q = k; q < e; ++q) gr.lds = std::max(gr.lds, ones_lds_bytes(tsdfs[order[q]]->g, gr.lk, P));
+        for (int q = k; q < e; ++q) gr.lds = std::max(gr.lds, batch_lds_bytes(tsdfs[order[q]]->g, gr.lk, P, U));
         gr.grid = batch_grid(P, U, gr.fmt, gr.lk, gr.end - gr.base, gr.lds);
         b->groups.push_back(gr);
         k = e;
