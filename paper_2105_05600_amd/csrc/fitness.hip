@@ -691,10 +691,11 @@ __global__ __launch_bounds__(kWave * WG) void k_fitness(FitLaunch a) {
 // Work items of the persistent batch kernel: 4 or 8 particle groups
 // (batch_waves) and one slice (points across the lanes), or 4 groups of 64
 // and one quarter of a slice (one particle per lane).  8 with the brick bits
-// staged; shapes of more than 16 evaluations per lane and step hold them in
+// staged; shapes of more than 16 evaluations per lane and step read them from
 // memory, with 4: two bodies in one kernel leave those too few registers (64
-// sequences in 128^3, 8 iterations: 4 x 8 6.8 ms with both, 5.1 without, 8 x 4
-// 4.7 and 3.7; 4 x 2 3.4 and 3.8).
+// sequences in 128^3, 8 iterations: 4 x 8 6.8 ms with both, 8 x 4 4.7; 5.2 and
+// 4.1 with one, 4 x 8 held to 4 wavefronts per SIMD: 5.7 with 3; 4 x 2 3.4 with
+// both, 3.8 with one).
 constexpr int batch_waves(int P, int U, int lk) {
     return P != kWave && P * U <= 16 && lk == ROSE_LOOKUP_NEAREST ? kPaWaves : 4;
 }
@@ -721,7 +722,8 @@ int fitness_blocks(const FitLaunch& L, int P, int U) { return blocks_of(L, P, ba
 // launch on the stream clears them, and every workgroup leaves once its
 // queue passes `end`.
 template <int P, int U, int FMT, int LK>
-__global__ __launch_bounds__(kWave * batch_waves(P, U, LK)) void k_fitness_batch(
+__global__ __launch_bounds__(kWave * batch_waves(P, U, LK),
+                             P == 4 && U == 8 && LK == ROSE_LOOKUP_NEAREST ? 4 : 0) void k_fitness_batch(
     const FitLaunch* __restrict__ seqs, const int* __restrict__ begin, int count, int base, int end,
     int* __restrict__ ctr, int ones_lds) {
     extern __shared__ __attribute__((aligned(16))) uint32_t s_dyn[];
